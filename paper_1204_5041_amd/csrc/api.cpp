@@ -154,12 +154,17 @@ struct csmap_sky {
   DevBuf d_boxes, d_blk_box, d_blk_count, d_blk_prefix, d_box_count, d_raw_off, d_blk_mask;
   DevBuf d_flat_off, d_flat_rec, d_flat_part;
   DevBuf d_udir;      // caller directions of csmap_render_dirs, x | y | z
+  DevBuf d_part;      // partial tiles of record slices (render; held by a captured graph)
+  DevBuf d_udir_part; // csmap_render_dirs: the same
   DevBuf d_rec32, d_phat64, d_rec64, d_orig;
   DevBuf d_tile_ptr, d_tile_boxes, d_items, d_box_items;
   std::vector<int64_t> box_items_off;  // per box offset into d_box_items (+ end)
   int64_t nblk = 0;
   int64_t ntiles = 0;
-  int64_t nitems_sorted = 0;
+  // Persistent schedule: work items, then the sliced tiles, in d_items, and
+  // the partial tiles they take in d_part.
+  int64_t nwork = 0, nsplit_tiles = 0, part_tiles = 0;
+  int32_t max_slices = 1;
   bool all_boxes = true;
   DevBuf d_counters;  // [0] pairs, [1] FP64 steps, [2] work counter (uint32), [3] middle steps,
                       // [4] all steps
@@ -225,6 +230,32 @@ bool use_blocks(const csmap_sky* s) { return s->tiling != 1; }
 
 // Rings per ring-block tile: 2 K rows of 32 pixels unless set.
 int block_rings(const csmap_sky* s) { return s->block_rings > 0 ? s->block_rings : 2 * s->K; }
+
+// Record slices.  A launch of fewer wavefronts than the chip holds leaves it
+// idle, and on an uneven sky the tiles that see most records finish last, so
+// a tile whose records are more than 1/kSliceItems of all tiles' is cut into
+// slices of about that size (kSliceItems is eight items per resident
+// wavefront at four wavefronts per SIMD), but of no fewer than
+// kSliceMinRecords records: about what setting up a tile and adding up its
+// partial sums cost.  Measured, one slice against this rule: Nside 64, 2,000
+// segments, FP64: 1509 us against 200 us; 1,003 directions and 100,000
+// segments, FP32C: 58.1 ms against 0.16 ms.
+constexpr double kSliceItems = 32768.0;
+constexpr double kSliceMinRecords = 64.0;
+// Share of a healpix-cone box's segments that its cone keeps, for planning
+// (0.13 on the stacking grids); the kept counts are not known on the host.
+constexpr double kConeShare = 0.13;
+
+int32_t slices_of(double cost, double total) {
+  const double most = cost / kSliceMinRecords;
+  const double want = cost * kSliceItems / std::max(total, 1.0);
+  if (want <= 1.25 || most < 2.0) return 1;
+  return (int32_t)std::ceil(std::min({want, most, 32768.0}));
+}
+
+double planned_records(const HostBox& h) {
+  return (double)h.n * (h.cone_nside > 0 ? kConeShare : 1.0);
+}
 
 // Rebuild descriptors, compaction tables, record storage and the tile plan.
 csmap_status prepare(csmap_sky* s) {
@@ -335,7 +366,7 @@ csmap_status prepare(csmap_sky* s) {
     for (auto& r : ranges[b])
       for (int64_t t = r.first; t <= r.second; ++t) {
         cnt[t + 1] += 1;
-        cost[t] += (double)s->boxes[b].n;
+        cost[t] += planned_records(s->boxes[b]);
       }
   }
   std::vector<int32_t> tile_ptr(s->ntiles + 1, 0), tile_boxes;
@@ -354,14 +385,34 @@ csmap_status prepare(csmap_sky* s) {
                              sizeof(int32_t) * tile_boxes.size(), hipMemcpyHostToDevice, st),
            "upload tiles");
   }
-  // Persistent schedule: tiles ordered by decreasing work.
+  // Persistent schedule: tiles in slices of about equal work, those of the
+  // costliest tiles first, and the list of sliced tiles behind them.
+  double total = 0.0;
+  for (double c : cost) total += c;
   std::vector<int32_t> order(s->ntiles);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(),
                    [&](int32_t a, int32_t b) { return cost[a] > cost[b]; });
-  s->nitems_sorted = s->ntiles;
-  HIPCHK(s, s->d_items.ensure(sizeof(int32_t) * std::max<int64_t>(s->ntiles, 1)), "alloc items");
-  HIPCHK(s, hipMemcpyAsync(s->d_items.p, order.data(), sizeof(int32_t) * s->ntiles,
+  std::vector<WorkItem> work, split;
+  work.reserve(s->ntiles);
+  int32_t slot = 0;
+  s->max_slices = 1;
+  for (int32_t t : order) {
+    const int32_t ns = slices_of(cost[t], total);
+    s->max_slices = std::max(s->max_slices, ns);
+    for (int32_t k = 0; k < ns; ++k) work.push_back({t, k, ns, slot});
+    if (ns == 1) continue;
+    split.push_back({t, 0, ns, slot});
+    slot += ns;
+  }
+  s->nwork = (int64_t)work.size();
+  s->nsplit_tiles = (int64_t)split.size();
+  s->part_tiles = slot;
+  work.insert(work.end(), split.begin(), split.end());
+  HIPCHK(s, s->d_part.ensure(sizeof(double) * (size_t)tile_pixels(s) * (size_t)slot),
+         "alloc partial tiles");
+  HIPCHK(s, s->d_items.ensure(sizeof(WorkItem) * work.size()), "alloc items");
+  HIPCHK(s, hipMemcpyAsync(s->d_items.p, work.data(), sizeof(WorkItem) * work.size(),
                            hipMemcpyHostToDevice, st), "upload items");
   // Per-box schedule: the tiles of each box.
   std::vector<int32_t> bitems;
@@ -439,6 +490,7 @@ FwdArgs fwd_args(csmap_sky* s, double* map) {
   A.chunk = s->chunk;
   A.accumulate = 0;
   A.only_box = -1;
+  A.nsplit = 1;
   A.map = map;
   A.pairs = s->d_counters.as<unsigned long long>();
   A.near_steps = s->d_counters.as<unsigned long long>() + 1;
@@ -462,8 +514,11 @@ csmap_status check_forward(const csmap_sky* s, const FwdArgs& A, int K) {
   } else if (t.blocks || t.tile_px != 64 * (int64_t)K) {
     return fail(CSMAP_E_STATE, "strip tiling does not match the launch");
   }
-  if (!A.items && A.nitems > t.ntiles)
+  if (!A.items && !A.work && A.nitems > t.ntiles)
     return fail(CSMAP_E_STATE, "more work items than tiles");
+  if (A.work && (A.nitems != s->nwork || A.nsplit_tiles != s->nsplit_tiles ||
+                 s->d_part.cap < sizeof(double) * 64 * (size_t)K * (size_t)s->part_tiles))
+    return fail(CSMAP_E_STATE, "record slices do not match the launch");
   return CSMAP_OK;
 }
 
@@ -485,6 +540,14 @@ csmap_status enqueue_render(csmap_sky* s, double* map, hipStream_t st, bool with
   const bool fp64 = s->form == CSMAP_FORM_FP64;
   const PreArgs P = pre_args(s);
   FwdArgs A = fwd_args(s, map);
+  if (s->schedule == 1) {
+    A.work = s->d_items.as<WorkItem>();
+    A.nitems = s->nwork;
+    A.split = s->nsplit_tiles ? A.work + s->nwork : nullptr;
+    A.nsplit_tiles = s->nsplit_tiles;
+    A.part = s->d_part.as<double>();
+    A.max_slices = s->max_slices;
+  }
   const csmap_status cs = check_forward(s, A, s->K);
   if (cs != CSMAP_OK) return cs;
   if (with_events) HIPCHK(s, hipEventRecord(s->ev[0], st), "event");
@@ -507,8 +570,6 @@ csmap_status enqueue_render(csmap_sky* s, double* map, hipStream_t st, bool with
       HIPCHK(s, launch_forward(fp64, s->K, false, A, grid, block, st), "forward launch");
     }
   } else if (s->schedule == 1) {
-    A.items = s->d_items.as<int32_t>();
-    A.nitems = s->nitems_sorted;
     HIPCHK(s, launch_forward(fp64, s->K, true, A, persistent_grid(s), block, st),
            "forward launch");
   } else {
@@ -581,6 +642,7 @@ csmap_status csmap_destroy_sky(csmap_sky* s) {
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
   DevBuf* bufs[] = {&s->raw, &s->d_boxes, &s->d_blk_box, &s->d_blk_count, &s->d_blk_prefix,
                     &s->d_blk_mask, &s->d_flat_off, &s->d_flat_rec, &s->d_udir, &s->d_flat_part,
+                    &s->d_part, &s->d_udir_part, &s->d_rows,
                     &s->d_box_count, &s->d_raw_off, &s->d_rec32, &s->d_phat64, &s->d_rec64,
                     &s->d_orig, &s->d_tile_ptr, &s->d_tile_boxes, &s->d_items,
                     &s->d_box_items, &s->d_counters, &s->d_pixtab32, &s->d_pix64,
@@ -1149,7 +1211,10 @@ csmap_status csmap_render_dirs(csmap_sky* s, int64_t n, const double* xyz, doubl
   // Strips of 64 K directions in the caller's order; every tile walks every
   // box, and the per-pixel visibility test of the kernels applies each
   // box's rule to each direction.
-  const int64_t tile_px = 64 * (int64_t)s->K;
+  // No more pixels per lane than give every lane of a tile a direction.
+  int K = s->K;
+  while (K > 1 && 64 * (int64_t)(K / 2) >= n) K /= 2;
+  const int64_t tile_px = 64 * (int64_t)K;
   const int64_t ntiles = (n + tile_px - 1) / tile_px;
   A.all_boxes = 1;
   A.rows = nullptr;
@@ -1162,6 +1227,19 @@ csmap_status csmap_render_dirs(csmap_sky* s, int64_t n, const double* xyz, doubl
   A.dirx = d;
   A.diry = d + n;
   A.dirz = d + 2 * n;
+  {
+    // Every tile walks every box, so all tiles take the same slices.
+    double records = 0.0;
+    for (const HostBox& h : s->boxes) records += planned_records(h);
+    A.nsplit = slices_of(records, records * (double)ntiles);
+    A.nitems = ntiles * A.nsplit;
+    if (A.nitems > INT32_MAX) return fail(CSMAP_E_STATE, "too many work items");
+    if (A.nsplit > 1)
+      HIPCHK(s, s->d_udir_part.ensure(sizeof(double) * (size_t)tile_px * (size_t)A.nitems),
+             "alloc partial sums");
+    A.part = s->d_udir_part.as<double>();
+    A.max_slices = A.nsplit;
+  }
   HIPCHK(s, launch_dirs_soa(n, xyz, d, d + n, d + 2 * n, st), "direction launch");
   HIPCHK(s, hipEventRecord(s->ev[0], st), "event");
   HIPCHK(s, launch_precompute(P, (int64_t)s->boxes.size(), st), "precompute launch");
@@ -1171,8 +1249,8 @@ csmap_status csmap_render_dirs(csmap_sky* s, int64_t n, const double* xyz, doubl
   HIPCHK(s, hipEventRecord(s->ev[1], st), "event");
   if (ntiles > 0) {
     const unsigned block = 64u * (unsigned)s->waves;
-    const unsigned grid = (unsigned)((ntiles + s->waves - 1) / s->waves);
-    HIPCHK(s, launch_forward(s->form == CSMAP_FORM_FP64, s->K, false, A, grid, block, st),
+    const unsigned grid = (unsigned)((A.nitems + s->waves - 1) / s->waves);
+    HIPCHK(s, launch_forward(s->form == CSMAP_FORM_FP64, K, false, A, grid, block, st),
            "forward launch");
   }
   HIPCHK(s, hipEventRecord(s->ev[2], st), "event");

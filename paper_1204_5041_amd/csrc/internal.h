@@ -113,6 +113,14 @@ struct FlatArgs {
 };
 constexpr int kFlatRec = 8;
 
+// A unit of forward work: slice `slice` of the `slices` into which the records
+// seen by a tile are cut (box_records).  With one slice the tile's sums go to
+// the map; otherwise to partial tile slot + slice (64 K doubles, pixel slot j
+// of lane l at 64 j + l), and k_fwd_combine adds the tile's slices in order.
+struct WorkItem {
+  int32_t tile, slice, slices, slot;
+};
+
 // Arguments of the forward pair kernels.
 struct FwdArgs {
   const DevBox* boxes;
@@ -142,6 +150,16 @@ struct FwdArgs {
   int32_t only_box;            // per-box schedule: the one box (else -1)
   int32_t frac;                // FP32C: fold far pairs into a running fraction
   int32_t seg_cap;             // >0: at most this many segments per box (tuning samples)
+  // Record slices (see WorkItem).  work: the items of the persistent
+  // schedule; null: item i is slice i % nsplit of tile i / nsplit (of items'
+  // tile when items is set).  part: the partial tiles; split: the sliced
+  // tiles that k_fwd_combine adds up (null: every tile, when nsplit > 1).
+  const WorkItem* work;
+  const WorkItem* split;
+  int64_t nsplit_tiles;
+  int32_t nsplit;
+  int32_t max_slices;          // most slices of any tile
+  double* part;
   double* map;
   unsigned long long* pairs;   // pair counter
   unsigned long long* near_steps;

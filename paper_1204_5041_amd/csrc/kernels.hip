@@ -544,10 +544,6 @@ __device__ __forceinline__ int64_t next_item(const FwdArgs& A, bool persistent, 
   return (int64_t)__builtin_amdgcn_readfirstlane(__shfl(it, 0));
 }
 
-__device__ __forceinline__ int32_t tile_of(const FwdArgs& A, int64_t item) {
-  return A.items ? ((ci32p)A.items)[item] : (int32_t)item;
-}
-
 // The pixels of one lane in a tile: slot j is pixel first + pos0 + j step,
 // present when pos0 + j step < cnt.  Ring-block tilings give each ring of
 // the tile 64 / G lanes (G rings per tile) and read the ring's row from the
@@ -585,6 +581,115 @@ __device__ __forceinline__ LaneRow lane_row(const FwdArgs& A, int64_t tile, int 
 __device__ __forceinline__ int32_t slot_off(const LaneRow& r, int j) {
   const int32_t pos = r.pos0 + j * r.step;
   return pos < r.cnt ? pos : (r.cnt > 0 ? r.cnt - 1 : 0);
+}
+
+// The records a work item takes: the records of every box its tile sees, one
+// box after another in runs of kSliceUnit (a box's last run may be short), cut
+// into w.slices nearly equal ranges of runs.  Whole runs keep a box's windows
+// of four records as they are in one slice.  The range's first box is found
+// by the wavefront's lanes, 64 boxes at a time: an item that asked every box
+// in turn would wait on one scalar load each.
+constexpr uint32_t kSliceUnit = 32;
+
+struct SliceRange {
+  uint32_t lo, hi;   // runs [lo, hi) of the tile's boxes
+  int32_t bi;        // first box entry to visit
+  uint32_t pos;      // runs before it
+};
+
+__device__ __forceinline__ uint32_t box_kept(const FwdArgs& A, int64_t b) {
+  const int64_t n = A.box_count[b].kept;
+  return (uint32_t)(A.seg_cap > 0 && n > A.seg_cap ? A.seg_cap : n);
+}
+
+__device__ __forceinline__ uint32_t runs_of(uint32_t records) {
+  return (records + kSliceUnit - 1) / kSliceUnit;
+}
+
+// Runs of the box of list entry bi (0 past the end): one entry per lane.
+__device__ __forceinline__ uint32_t entry_runs(const FwdArgs& A, bool list, int32_t bi,
+                                               int32_t b1) {
+  if (bi >= b1) return 0;
+  return runs_of(box_kept(A, list ? A.tile_boxes[bi] : bi));
+}
+
+__device__ __forceinline__ SliceRange slice_range(const FwdArgs& A, const WorkItem& w, bool list,
+                                                  int32_t b0, int32_t b1, int lane) {
+  SliceRange r = {0u, ~0u, b0, 0u};
+  if (w.slices <= 1) return r;
+  uint32_t total = 0;
+  for (int32_t c = b0; c < b1; c += 64) {
+    uint32_t u = entry_runs(A, list, c + lane, b1);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) u += __shfl_xor(u, off);
+    total += (uint32_t)__builtin_amdgcn_readfirstlane((int)u);
+  }
+  r.lo = (uint32_t)((uint64_t)total * (uint32_t)w.slice / (uint32_t)w.slices);
+  r.hi = (uint32_t)((uint64_t)total * ((uint32_t)w.slice + 1) / (uint32_t)w.slices);
+  if (r.lo == 0) return r;
+  uint32_t before = 0;
+  for (int32_t c = b0; c < b1; c += 64) {
+    const uint32_t u = entry_runs(A, list, c + lane, b1);
+    uint32_t incl = u;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t o = __shfl_up(incl, off);
+      if (lane >= off) incl += o;
+    }
+    const unsigned long long past = __ballot(before + incl > r.lo);
+    if (past) {
+      const int l = __builtin_ctzll(past);
+      r.bi = c + l;
+      r.pos = before + (uint32_t)__builtin_amdgcn_readlane((int)(incl - u), l);
+      return r;
+    }
+    before += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+  }
+  r.bi = b1;
+  return r;
+}
+
+// Records [r0, r1) of box b inside the range (r1 <= r0: none), moving past it.
+__device__ __forceinline__ void box_records(const FwdArgs& A, int32_t b, SliceRange& r,
+                                            int64_t& r0, int64_t& r1) {
+  r0 = ((cbox_p)A.boxes + b)->rec_off;
+  const int64_t kept = load_kept(A.box_count, b);
+  const uint32_t n = (uint32_t)(A.seg_cap > 0 && kept > A.seg_cap ? A.seg_cap : kept);
+  const uint32_t u = runs_of(n);
+  const uint32_t u0 = r.lo > r.pos ? r.lo - r.pos : 0;
+  const uint32_t u1 = r.hi - r.pos < u ? r.hi - r.pos : u;
+  r.pos += u;
+  r1 = r0 + (u1 < u ? u1 * kSliceUnit : n);
+  r0 += u0 * kSliceUnit;
+}
+
+// Work item `item` (uniform over the wavefront).
+__device__ __forceinline__ WorkItem work_item(const FwdArgs& A, int64_t item) {
+  WorkItem w;
+  if (A.work) {
+    const ci32p p = (ci32p)(A.work + item);
+    w.tile = p[0];
+    w.slice = p[1];
+    w.slices = p[2];
+    w.slot = p[3];
+  } else {
+    // 32-bit division: the launcher keeps the items below 2^31.
+    const uint32_t at = (uint32_t)item / (uint32_t)A.nsplit;
+    w.slice = (int32_t)((uint32_t)item - at * (uint32_t)A.nsplit);
+    w.tile = A.items ? ((ci32p)A.items)[at] : (int32_t)at;
+    w.slices = A.nsplit;
+    w.slot = (int32_t)(at * (uint32_t)A.nsplit);
+  }
+  return w;
+}
+
+// Where the sum of pixel p (slot j of this lane) goes: the map, or the
+// slice's partial tile.
+template <int K>
+__device__ __forceinline__ void store_pixel(const FwdArgs& A, const WorkItem& w, int64_t p, int j,
+                                            int lane, double v) {
+  if (w.slices > 1) A.part[(int64_t)(w.slot + w.slice) * (64 * K) + 64 * j + lane] = v;
+  else A.map[p] = A.accumulate ? A.map[p] + v : v;
 }
 
 // Fold the term m/d into the running fraction fp/fq of a window; the first
@@ -775,7 +880,7 @@ __global__ void __launch_bounds__(256) k_fwd32(FwdArgs A) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int64_t item = PERSISTENT ? next_item(A, true, lane, 0, 0) : (int64_t)blockIdx.x * wpb + wave;
   const int64_t stride = (int64_t)gridDim.x * wpb;
-  unsigned long long near_steps = 0, mid_steps = 0, all_steps = 0;
+  unsigned long long near_steps = 0, mid_steps = 0, all_steps = 0, pairs = 0;
   const float near_w = A.near_w, far_w = A.far_w;
   cf4p recs = (cf4p)A.rec32;
   cd2p ph64 = (cd2p)A.phat64;
@@ -783,7 +888,8 @@ __global__ void __launch_bounds__(256) k_fwd32(FwdArgs A) {
   extern __shared__ double sdir_all[];
   double* const sdir = sdir_all + wave * (K * 3 * 64);
   while (item < A.nitems) {
-    const int64_t tile = tile_of(A, item);
+    const WorkItem wi = work_item(A, item);
+    const int64_t tile = wi.tile;
     // Pixel directions come from the table written by the RING pix2vec
     // kernel.  Slots past the end of a lane's row repeat its last pixel
     // (they are masked out of every sum and never written).  The FP64
@@ -818,8 +924,13 @@ __global__ void __launch_bounds__(256) k_fwd32(FwdArgs A) {
     int32_t b0 = 0, b1 = A.nbox;
     if (A.only_box >= 0) { b0 = A.only_box; b1 = A.only_box + 1; }
     else if (!A.all_boxes) { b0 = ((ci32p)A.tile_ptr)[tile]; b1 = ((ci32p)A.tile_ptr)[tile + 1]; }
-    for (int32_t bi = b0; bi < b1; ++bi) {
-      const int32_t b = (A.all_boxes || A.only_box >= 0) ? bi : ((ci32p)A.tile_boxes)[bi];
+    const bool list = !A.all_boxes && A.only_box < 0;
+    SliceRange sr = slice_range(A, wi, list, b0, b1, lane);
+    for (int32_t bi = sr.bi; bi < b1 && sr.pos < sr.hi; ++bi) {
+      const int32_t b = list ? ((ci32p)A.tile_boxes)[bi] : bi;
+      int64_t r0, r1;
+      box_records(A, b, sr, r0, r1);
+      if (r1 <= r0) continue;
       const DevBox bx = load_box(A.boxes, b);
       // Visibility as a per-lane 0/1 weight: partial sums of pixels that do
       // not see the box are multiplied by 0 before they reach the running
@@ -836,11 +947,7 @@ __global__ void __launch_bounds__(256) k_fwd32(FwdArgs A) {
         nvis += __popcll(__ballot(v));
       }
       if (nvis == 0) continue;
-      const int64_t r0 = bx.rec_off;
-      int64_t r1 = r0 + load_kept(A.box_count, b);
-      if (A.seg_cap > 0 && r1 - r0 > A.seg_cap) r1 = r0 + A.seg_cap;
-      if (lane == 0 && r1 > r0) atomicAdd(A.pairs, nvis * (unsigned long long)(r1 - r0));
-      if (r1 == r0) continue;
+      pairs += nvis * (unsigned long long)(r1 - r0);
       all_steps += (unsigned long long)(r1 - r0);
       if constexpr (FRAC) {
         if (ring)
@@ -952,12 +1059,14 @@ __global__ void __launch_bounds__(256) k_fwd32(FwdArgs A) {
         // The running sum s carries the result; c is the negated rounding
         // error still owed to it, so the value is s - c.
         const int64_t p = lw.first + lw.pos0 + j * lw.step;
-        const double v = (double)S[j] - (double)C[j];
-        A.map[p] = A.accumulate ? A.map[p] + v : v;
+        store_pixel<K>(A, wi, p, j, lane, (double)S[j] - (double)C[j]);
       }
     }
     item = PERSISTENT ? next_item(A, true, lane, item, stride) : item + stride;
   }
+  // One atomic per wavefront and counter: per box and tile they queued up on
+  // one address.
+  if (lane == 0 && pairs) atomicAdd(A.pairs, pairs);
   if (lane == 0 && near_steps) atomicAdd(A.near_steps, near_steps);
   if (lane == 0 && mid_steps) atomicAdd(A.mid_steps, mid_steps);
   if (lane == 0 && all_steps) atomicAdd(A.steps, all_steps);
@@ -1044,8 +1153,10 @@ __global__ void __launch_bounds__(256) k_fwd64(FwdArgs A) {
   int64_t item = PERSISTENT ? next_item(A, true, lane, 0, 0) : (int64_t)blockIdx.x * wpb + wave;
   const int64_t stride = (int64_t)gridDim.x * wpb;
   cd2p recs = (cd2p)A.rec64;
+  unsigned long long pairs = 0;
   while (item < A.nitems) {
-    const int64_t tile = tile_of(A, item);
+    const WorkItem wi = work_item(A, item);
+    const int64_t tile = wi.tile;
     double nd[K][3];
     bool inmap[K];
     bool same_ring = true;   // this lane's K pixels share one ring (one z)
@@ -1067,26 +1178,23 @@ __global__ void __launch_bounds__(256) k_fwd64(FwdArgs A) {
     int32_t b0 = 0, b1 = A.nbox;
     if (A.only_box >= 0) { b0 = A.only_box; b1 = A.only_box + 1; }
     else if (!A.all_boxes) { b0 = ((ci32p)A.tile_ptr)[tile]; b1 = ((ci32p)A.tile_ptr)[tile + 1]; }
-    for (int32_t bi = b0; bi < b1; ++bi) {
-      const int32_t b = (A.all_boxes || A.only_box >= 0) ? bi : ((ci32p)A.tile_boxes)[bi];
+    const bool list = !A.all_boxes && A.only_box < 0;
+    SliceRange sr = slice_range(A, wi, list, b0, b1, lane);
+    for (int32_t bi = sr.bi; bi < b1 && sr.pos < sr.hi; ++bi) {
+      const int32_t b = list ? ((ci32p)A.tile_boxes)[bi] : bi;
+      int64_t r0, r1;
+      box_records(A, b, sr, r0, r1);
+      if (r1 <= r0) continue;
       const DevBox bx = load_box(A.boxes, b);
       bool vis[K];
-      bool anyv = false;
+      unsigned long long nvis = 0;
 #pragma unroll
       for (int j = 0; j < K; ++j) {
         vis[j] = inmap[j] && (bx.vis == 0 || sees_box(nd[j][0], nd[j][1], nd[j][2], bx, A.eta0));
-        anyv |= vis[j];
+        nvis += __popcll(__ballot(vis[j]));
       }
-      if (!__any(anyv)) continue;
-      const int64_t r0 = bx.rec_off;
-      int64_t r1 = r0 + load_kept(A.box_count, b);
-      if (A.seg_cap > 0 && r1 - r0 > A.seg_cap) r1 = r0 + A.seg_cap;
-      {
-        unsigned long long nvis = 0;
-#pragma unroll
-        for (int j = 0; j < K; ++j) nvis += __popcll(__ballot(vis[j]));
-        if (lane == 0 && r1 > r0) atomicAdd(A.pairs, nvis * (unsigned long long)(r1 - r0));
-      }
+      if (nvis == 0) continue;
+      pairs += nvis * (unsigned long long)(r1 - r0);
       for (int64_t c0 = r0; c0 < r1; c0 += A.chunk) {
         const int64_t c1 = (c0 + A.chunk < r1) ? c0 + A.chunk : r1;
         double part[K];
@@ -1113,12 +1221,53 @@ __global__ void __launch_bounds__(256) k_fwd64(FwdArgs A) {
     for (int j = 0; j < K; ++j) {
       if (lw.pos0 + j * lw.step < lw.cnt) {
         const int64_t p = lw.first + lw.pos0 + j * lw.step;
-        const double v = S[j] - C[j];
-        A.map[p] = A.accumulate ? A.map[p] + v : v;
+        store_pixel<K>(A, wi, p, j, lane, S[j] - C[j]);
       }
     }
     item = PERSISTENT ? next_item(A, true, lane, item, stride) : item + stride;
   }
+  if (lane == 0 && pairs) atomicAdd(A.pairs, pairs);
+}
+
+// The map's pixels of the sliced tiles: each the sum of its tile's partial
+// sums.  A workgroup takes one pixel slot j of a tile's 64 lanes; its
+// wavefronts each add a run of the slices in order, eight loads in flight,
+// and the runs' sums are added in order.  The loads' latency bounds it (one
+// wavefront adding 782 slices of two tiles took 1.5 ms), hence the
+// wavefronts per workgroup grow with the slices.
+template <int K>
+__global__ void __launch_bounds__(1024) k_fwd_combine(FwdArgs A) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int32_t i = (int32_t)(blockIdx.x / K);
+  const int j = (int)(blockIdx.x % K);
+  int32_t tile = i, slices = A.nsplit, slot = i * A.nsplit;
+  if (A.split) {
+    const ci32p p = (ci32p)(A.split + i);
+    tile = p[0];
+    slices = p[2];
+    slot = p[3];
+  }
+  __shared__ double sum[16][64];
+  const int32_t s0 = slices * wave / nw, s1 = slices * (wave + 1) / nw;
+  const double* part = A.part + (int64_t)(slot + s0) * (64 * K) + 64 * j + lane;
+  double v = 0.0;
+  int32_t s = s0;
+  for (; s + 8 <= s1; s += 8, part += 8 * 64 * K) {
+    double t[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) t[q] = part[q * 64 * K];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v += t[q];
+  }
+  for (; s < s1; ++s, part += 64 * K) v += *part;
+  sum[wave][lane] = v;
+  __syncthreads();
+  if (wave != 0) return;
+  for (int w = 1; w < nw; ++w) v += sum[w][lane];
+  const LaneRow lr = lane_row<K>(A, tile, lane);
+  const int32_t at = lr.pos0 + j * lr.step;
+  if (at < lr.cnt) A.map[lr.first + at] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -1515,6 +1664,19 @@ hipError_t launch_forward(bool fp64, int K, bool persistent, const FwdArgs& A, u
     case 8: persistent ? fwd_launch<8, true>(fp64, A, grid, block, st)
                        : fwd_launch<8, false>(fp64, A, grid, block, st); break;
     default: return hipErrorInvalidValue;
+  }
+  const int64_t nt = A.split ? A.nsplit_tiles : (A.nsplit > 1 ? A.nitems / A.nsplit : 0);
+  if (nt > 0) {
+    // About eight slices (one round of loads) per wavefront, at most 16.
+    int nw = 1;
+    while (nw < 16 && 8 * nw < A.max_slices) nw *= 2;
+    const dim3 cg((unsigned)(nt * K)), cb(64 * nw);
+    switch (K) {
+      case 1: k_fwd_combine<1><<<cg, cb, 0, st>>>(A); break;
+      case 2: k_fwd_combine<2><<<cg, cb, 0, st>>>(A); break;
+      case 4: k_fwd_combine<4><<<cg, cb, 0, st>>>(A); break;
+      case 8: k_fwd_combine<8><<<cg, cb, 0, st>>>(A); break;
+    }
   }
   return hipGetLastError();
 }
