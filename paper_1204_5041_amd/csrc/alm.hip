@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "healpix_dev.h"
@@ -150,9 +151,9 @@ struct cplx {
   double r, i;
 };
 
-// The ring transforms of step 1 share one FFT over P = 2^e <= kFftMaxP
-// complex points in LDS, taken by a workgroup of kFftThreads threads in
-// radix-8 passes (one radix-2 or radix-4 pass when e is not a multiple of
+// The ring transforms of step 1 share one FFT over P = 2^e <= 8 T complex
+// points in LDS, taken by T threads (64, 512 or 1024: at most one radix-8
+// butterfly per thread and pass) in radix-8 passes (one radix-2 or radix-4 pass when e is not a multiple of
 // 3), each thread taking one butterfly in registers per pass: forward by
 // decimation in frequency (natural order in, digit-reversed order out),
 // inverse by decimation in time with the passes reversed (digit-reversed
@@ -168,19 +169,23 @@ struct cplx {
 // It costs an address computation per access, which pays where LDS bounds
 // the kernel (the belt rings) and not where latency does (the cap rings,
 // whose nine transforms per workgroup run at the same speed either way).
-// ftab[k] = e^{-2 pi i k/kFftMaxP}, k < kFftMaxP/4, a quarter of the
+// ftab[k] = e^{-2 pi i k/kTwP}, k < kTwP/4, a quarter of the
 // period: a workgroup copies it into LDS and forms every twiddle from it,
-// e^{-2 pi i (q kFftMaxP/4 + r)/kFftMaxP} = (-i)^q e^{-2 pi i r/kFftMaxP}
+// e^{-2 pi i (q kTwP/4 + r)/kTwP} = (-i)^q e^{-2 pi i r/kTwP}
 // (a swap and sign changes, exact).  Read from global memory, the seven
 // twiddles of each butterfly waited on the L2 in every pass: the two ring
 // kernels took 30% and 20% longer than with constant twiddles.
-constexpr int kFftThreads = 512;
-constexpr int64_t kFftMaxP = 4096;   // 64 KB of LDS, and 16 KB for the twiddles
-constexpr int kTwQ = (int)(kFftMaxP / 4);
+// Transforms of 2 kTwP points take half-steps of the table in their first
+// pass: an odd power is the table's entry below it times e^{-2 pi i/(2 kTwP)}.
+constexpr int64_t kFftMaxP = 8192;   // 128 KB of LDS, and 16 KB for the twiddles
+constexpr int kTwP = 4096;
+constexpr int kTwQ = kTwP / 4;
+constexpr double kHalfC = 0.99999970586288222663;    // cos(2 pi / 8192), rounded
+constexpr double kHalfS = 0.00076699031874270452694; // sin(2 pi / 8192), rounded
 
 // LDS bytes of a workgroup transforming P points: the quarter twiddle
-// table, then the points (gfx950 gives a workgroup up to 160 KB, so two of
-// the largest share a CU).
+// table, then the points (gfx950 gives a workgroup up to 160 KB: two of 4096
+// points share a CU, one of 8192 points takes it).
 constexpr size_t fft_lds_bytes(int64_t P) { return 16 * (size_t)(kTwQ + P); }
 
 // Slot of quarter-table entry r (< 1024) in LDS: bits 4-9 folded into bits
@@ -192,11 +197,11 @@ __device__ __forceinline__ int tw_slot(int r) { return r ^ ((r >> 4) & 15) ^ (r 
 
 // Copies the quarter table into LDS (tl); the caller synchronises.
 __device__ __forceinline__ void fft_load_twiddles(double* tl, const double* ftab) {
-  for (int k = threadIdx.x; k < kTwQ; k += kFftThreads)
+  for (int k = threadIdx.x; k < kTwQ; k += blockDim.x)
     reinterpret_cast<double2*>(tl)[tw_slot(k)] = reinterpret_cast<const double2*>(ftab)[k];
 }
 
-// e^{-2 pi i k/kFftMaxP}, 0 <= k < kFftMaxP, from the quarter table.
+// e^{-2 pi i k/kTwP}, 0 <= k < kTwP, from the quarter table.
 __device__ __forceinline__ cplx fft_twiddle(const double* tl, int k) {
   const int q = k >> 10, r = k & (kTwQ - 1);
   static_assert(kTwQ == 1024, "quarter index");
@@ -226,7 +231,7 @@ __device__ void fft_twiddles_block(double* ftab, int64_t blk) {
   const int64_t k = blk * 256 + threadIdx.x;
   if (k >= kTwQ) return;
   double sp, cp;
-  sincospi((double)(2 * k) / (double)kFftMaxP, &sp, &cp);
+  sincospi((double)(2 * k) / (double)kTwP, &sp, &cp);
   ftab[2 * k] = cp;
   ftab[2 * k + 1] = -sp;
 }
@@ -288,11 +293,14 @@ __device__ __forceinline__ void dft_small(cplx* x) {
 // y_q' = e^{-2 pi i p q'/S} sum_q x_{p + q h} e^{-2 pi i q q'/R}, written at
 // p + q' h.  The inverse pass undoes it up to a factor R: twiddles
 // conjugated and applied first, then the inverse R-point DFT.
-template <int R, bool kInv, bool kSwz>
-__device__ __forceinline__ void fft_pass(double* x, int P, int S, const double* tl) {
+template <int R, bool kInv, bool kSwz, int T>
+__device__ __forceinline__ void fft_pass(double* x, int P, int S, const double* tl, int thr) {
+  // Powers of e^{-2 pi i/S} in table steps: 2 kTwP / S half-steps where the
+  // transform may hold 8192 points, whole steps otherwise.
+  constexpr int kPeriod = T > 512 ? 2 * kTwP : kTwP;
   const int h = S / R;
-  const int tw = (int)kFftMaxP / S;   // table step of e^{-2 pi i/S}
-  for (int b = threadIdx.x; b < P / R; b += kFftThreads) {
+  const int tw = kPeriod / S;
+  for (int b = thr; b < P / R; b += T) {
     const int pos = b & (h - 1);
     const int base = (b - pos) * R + pos;
     cplx v[R];
@@ -301,7 +309,14 @@ __device__ __forceinline__ void fft_pass(double* x, int P, int S, const double* 
     if constexpr (!kInv) dft_small<R, false>(v);
 #pragma unroll
     for (int q = 1; q < R; ++q) {
-      const cplx t = fft_twiddle(tl, (pos * q * tw) & ((int)kFftMaxP - 1));
+      const int k = (pos * q * tw) & (kPeriod - 1);
+      cplx t;
+      if constexpr (T > 512) {
+        t = fft_twiddle(tl, k >> 1);
+        if (k & 1) t = cmul(t, cplx{kHalfC, -kHalfS});
+      } else {
+        t = fft_twiddle(tl, k);
+      }
       const cplx w = {t.r, kInv ? -t.i : t.i};
       v[q] = cmul(v[q], w);
     }
@@ -312,33 +327,33 @@ __device__ __forceinline__ void fft_pass(double* x, int P, int S, const double* 
   __syncthreads();
 }
 
-// Forward transform of P (a power of two <= kFftMaxP) values in LDS,
+// Forward transform of P (a power of two <= 8 T) values in LDS by T threads,
 // natural order in, digit-reversed order out: radix-8 passes from the
 // widest span down, then one radix-4 or radix-2 pass if log2 P mod 3 is 2
 // or 1.
-template <bool kSwz>
-__device__ void fft_dif(double* x, int P, const double* tl) {
+template <bool kSwz, int T>
+__device__ void fft_dif(double* x, int P, const double* tl, int thr) {
   int S = P;
   while (S >= 8) {
-    fft_pass<8, false, kSwz>(x, P, S, tl);
+    fft_pass<8, false, kSwz, T>(x, P, S, tl, thr);
     S >>= 3;
   }
-  if (S == 4) fft_pass<4, false, kSwz>(x, P, 4, tl);
-  if (S == 2) fft_pass<2, false, kSwz>(x, P, 2, tl);
+  if (S == 4) fft_pass<4, false, kSwz, T>(x, P, 4, tl, thr);
+  if (S == 2) fft_pass<2, false, kSwz, T>(x, P, 2, tl, thr);
 }
 
 // Inverse of fft_dif times P: digit-reversed order in, natural order out,
 // the passes in reverse order.
-template <bool kSwz>
-__device__ void fft_dit_inv(double* x, int P, const double* tl) {
+template <bool kSwz, int T>
+__device__ void fft_dit_inv(double* x, int P, const double* tl, int thr) {
   int e = 0;
   while ((1 << e) < P) ++e;
   int S = 1 << (e % 3);
-  if (S == 4) fft_pass<4, true, kSwz>(x, P, 4, tl);
-  if (S == 2) fft_pass<2, true, kSwz>(x, P, 2, tl);
+  if (S == 4) fft_pass<4, true, kSwz, T>(x, P, 4, tl, thr);
+  if (S == 2) fft_pass<2, true, kSwz, T>(x, P, 2, tl, thr);
   while (S < P) {
     S <<= 3;
-    fft_pass<8, true, kSwz>(x, P, S, tl);
+    fft_pass<8, true, kSwz, T>(x, P, S, tl, thr);
   }
 }
 
@@ -363,7 +378,7 @@ __device__ __forceinline__ int dif_pos(int k, int e) {
 // X_k = conj X_{L-k} above.  F_m = X_{m mod L}, times e^{-i pi m/L} on
 // rings with the half-pixel offset.  tab[k] = e^{-i pi k/L}, k = 0 .. L.
 // One workgroup per ring.
-constexpr int64_t kBeltMaxH = kFftMaxP;   // H <= 4096: Nside <= 2048
+constexpr int64_t kBeltMaxH = kFftMaxP;   // H <= 8192: Nside <= 4096
 
 __device__ void fft_table_block(int64_t L, double* tab, int64_t blk) {
   const int64_t k = blk * 256 + threadIdx.x;
@@ -374,9 +389,10 @@ __device__ void fft_table_block(int64_t L, double* tab, int64_t blk) {
   tab[2 * k + 1] = -sp;
 }
 
-__global__ void __launch_bounds__(kFftThreads) k_ring_fft(int64_t nside, int64_t mmax,
-                                                          const double* map, const double* tab,
-                                                          const double* ftab, double* F) {
+template <int T>
+__global__ void __launch_bounds__(T) k_ring_fft(int64_t nside, int64_t mmax, const double* map,
+                                                const double* tab, const double* ftab,
+                                                double* F) {
   extern __shared__ double sm[];   // quarter twiddle table, then H points
   double* tl = sm;
   double* zs = sm + 2 * kTwQ;      // H complex values at fft_slot<true> positions
@@ -386,11 +402,11 @@ __global__ void __launch_bounds__(kFftThreads) k_ring_fft(int64_t nside, int64_t
   const int L = (int)r.len, H = L / 2;
   const int e = __builtin_ctz((unsigned)H);
   const double* x = map + r.first;
-  for (int n = threadIdx.x; n < H; n += kFftThreads) fft_put<true>(zs, n, {x[2 * n], x[2 * n + 1]});
+  for (int n = threadIdx.x; n < H; n += T) fft_put<true>(zs, n, {x[2 * n], x[2 * n + 1]});
   __syncthreads();
-  fft_dif<true>(zs, H, tl);
+  fft_dif<true, T>(zs, H, tl, threadIdx.x);
   double* out = F + 2 * (i - 1) * (mmax + 1);
-  for (int m = threadIdx.x; m <= (int)mmax; m += kFftThreads) {
+  for (int m = threadIdx.x; m <= (int)mmax; m += T) {
     int k = (int)((unsigned)m % (unsigned)L);
     const bool upper = k > H;
     if (upper) k = L - k;
@@ -415,11 +431,14 @@ __global__ void __launch_bounds__(kFftThreads) k_ring_fft(int64_t nside, int64_t
   }
 }
 
-// Step 1 for the polar-cap rings (Nside <= 2048).  North ring i and south
-// ring 4N - i both have L = 4i pixels at azimuths 2 pi (j + 1/2)/L; they are
-// taken together as z_j = x^N_j + i x^S_j, whose DFT Z gives both:
-// X^N_k = (Z_k + conj Z_{L-k})/2, X^S_k = (Z_k - conj Z_{L-k})/(2i), and
-// F_m = e^{-i pi m/L} X_{m mod L}.  L = 4i is split by four (j = 4n + r):
+// Step 1 for ring pairs of any length, Nside <= 4096: the polar caps, and the
+// belt when Nside is not a power of two.  North ring q and south ring 4N - q
+// both have L = 4i pixels, i = min(q, N), at azimuths 2 pi (j + 1/2)/L, or
+// 2 pi j/L on every other belt ring; they are taken together as
+// z_j = x^N_j + i x^S_j (the equator ring alone, x^S = 0), whose DFT Z gives
+// both: X^N_k = (Z_k + conj Z_{L-k})/2, X^S_k = (Z_k - conj Z_{L-k})/(2i), and
+// F_m = X_{m mod L}, times e^{-i pi m/L} with the half-pixel offset.
+// L = 4i is split by four (j = 4n + r):
 // Z_{kappa + s i} = sum_r (-i)^{rs} e^{-2 pi i r kappa/L} D_r(kappa), D_r the
 // length-i DFT of z_{4n+r}.  i is arbitrary, so each D_r is taken by
 // Bluestein's chirp transform: with w_n = e^{-i pi n^2/i} (from n^2 mod 2i,
@@ -430,11 +449,16 @@ __global__ void __launch_bounds__(kFftThreads) k_ring_fft(int64_t nside, int64_t
 // The filter's transform stays in registers over the four D_r, and D_r
 // stays in registers until the radix-4 step; Z goes through a global slot
 // of 4i values before the unpacking, which pairs k with L - k.  One
-// workgroup per ring pair.
-constexpr int kCapPer = (int)(kFftMaxP / kFftThreads);  // transform positions per thread
-constexpr int kCapKappa = kCapPer / 2;                  // D_r values per thread (i <= kFftMaxP / 2)
+// workgroup per ring pair: T threads take the four D_r one after another, or
+// with kQuad four groups of T threads take one each, each in its own P points
+// of LDS.  Transforms of few points wait on LDS and barriers, not on work, so
+// they run the four side by side (the 127 ring pairs of Nside 128: 17.0 us
+// with four wavefronts, 27.4 us with 512 threads taking the four in turn).
+constexpr int kCapPer = 8;             // transform positions per thread
+constexpr int kCapKappa = kCapPer / 2; // D_r values per thread (i <= 4 T)
+constexpr int64_t kChirpBeltMin = 1024;   // Nside * (lmax / 64) from which the belt takes it
 
-__device__ __forceinline__ int64_t pow2_at_least(int64_t v) {
+__host__ __device__ __forceinline__ int64_t pow2_at_least(int64_t v) {
   int64_t p = 1;
   while (p < v) p <<= 1;
   return p;
@@ -448,21 +472,23 @@ __device__ __forceinline__ void chirp(int64_t n, int64_t len, double& c, double&
   s = -sp;
 }
 
-__global__ void __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
-k_cap_bluestein(int64_t nside, int64_t mmax, const double* map, const double* ftab,
-                double* zslot, double* F) {
-  extern __shared__ double sm[];   // quarter twiddle table, then P points
+template <int T, bool kQuad>
+__device__ void ring_chirp(double* sm, int64_t nside, int64_t mmax, const double* map,
+                           const double* ftab, double* zslot, double* F, int64_t rn) {
   double* tl = sm;
-  double* xs = sm + 2 * kTwQ;      // P complex values, in order
   fft_load_twiddles(tl, ftab);
-  const int t = threadIdx.x;
-  const int64_t N = nside, i = 1 + blockIdx.x, L = 4 * i;
+  const int t = kQuad ? threadIdx.x % T : threadIdx.x;
+  const int quad = kQuad ? threadIdx.x / T : 0;
+  const int64_t N = nside, i = rn < N ? rn : N, L = 4 * i;
   const int P = (int)pow2_at_least(2 * i - 1);
+  double* xs = sm + 2 * kTwQ + 2 * (int64_t)quad * P;   // P complex values, in order
   const double inv_p = 1.0 / (double)P;   // exact: P is a power of two
-  const double* xn = map + 2 * i * (i - 1);
-  const double* xsth = map + 12 * N * N - 2 * i * (i + 1);
+  const Ring ring = ring_of(N, rn);
+  const bool pair = rn != 2 * N;           // the equator ring has no partner
+  const double* xn = map + ring.first;
+  const double* xsth = map + ring_of(N, 4 * N - rn).first;
   // Chirp filter b_m = conj(w_m) at m mod P for |m| < i, then its transform.
-  for (int p = t; p < P; p += kFftThreads) {
+  for (int p = t; p < P; p += T) {
     const int64_t n = p < i ? p : (p > P - i ? P - p : -1);
     double br = 0.0, bi = 0.0;
     if (n >= 0) {
@@ -474,24 +500,24 @@ k_cap_bluestein(int64_t nside, int64_t mmax, const double* map, const double* ft
     fft_put<false>(xs, p, {br, bi});
   }
   __syncthreads();
-  fft_dif<false>(xs, P, tl);
+  fft_dif<false, T>(xs, P, tl, t);
   double Br[kCapPer], Bi[kCapPer];
 #pragma unroll
   for (int j = 0; j < kCapPer; ++j) {
-    const int p = t + j * kFftThreads;
+    const int p = t + j * T;
     const cplx b = p < P ? fft_get<false>(xs, p) : cplx{0.0, 0.0};
     Br[j] = b.r;
     Bi[j] = b.i;
   }
   __syncthreads();
   // The chirp w_n and the twist e^{-2 pi i n/L} at this thread's positions
-  // n = t + j * kFftThreads < i, shared by the four quarter-length DFTs:
+  // n = t + j * T < i, shared by the four quarter-length DFTs:
   // the inputs y_n w_n, the outputs w_kappa (...) and the twist powers
   // e^{-2 pi i r kappa/L} = (e^{-2 pi i kappa/L})^r.
   double wc[kCapKappa], ws[kCapKappa], tc[kCapKappa], ts[kCapKappa];
 #pragma unroll
   for (int j = 0; j < kCapKappa; ++j) {
-    const int64_t n = t + (int64_t)j * kFftThreads;
+    const int64_t n = t + (int64_t)j * T;
     wc[j] = ws[j] = tc[j] = ts[j] = 0.0;
     if (n < i) {
       chirp(n, i, wc[j], ws[j]);
@@ -504,16 +530,17 @@ k_cap_bluestein(int64_t nside, int64_t mmax, const double* map, const double* ft
   // E_r(kappa) = e^{-2 pi i r kappa / L} D_r(kappa), staged in the ring's Z
   // slot at r i + kappa: the radix-4 step below reads back, from the same
   // thread, exactly the four positions kappa + s i that it then writes.
-  double* Z = zslot + 2 * (2 * i * (i - 1));
+  double* Z = zslot + (rn < N ? 4 * rn * (rn - 1) : 8 * N * (int64_t)blockIdx.x);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
+  for (int rr = 0; rr < (kQuad ? 1 : 4); ++rr) {
+    const int r = kQuad ? quad : rr;
 #pragma unroll
     for (int j = 0; j < kCapPer; ++j) {
-      const int p = t + j * kFftThreads;
+      const int p = t + j * T;
       if (p < P) {
         double ar = 0.0, ai = 0.0;
         if (j < kCapKappa && p < i) {
-          const double yr = xn[4 * p + r], yi = xsth[4 * p + r];
+          const double yr = xn[4 * p + r], yi = pair ? xsth[4 * p + r] : 0.0;
           ar = fma(yr, wc[j], -(yi * ws[j]));
           ai = fma(yr, ws[j], yi * wc[j]);
         }
@@ -521,20 +548,20 @@ k_cap_bluestein(int64_t nside, int64_t mmax, const double* map, const double* ft
       }
     }
     __syncthreads();
-    fft_dif<false>(xs, P, tl);
+    fft_dif<false, T>(xs, P, tl, t);
 #pragma unroll
     for (int j = 0; j < kCapPer; ++j) {
-      const int p = t + j * kFftThreads;
+      const int p = t + j * T;
       if (p < P) {
         const cplx a = fft_get<false>(xs, p);
         fft_put<false>(xs, p, {fma(a.r, Br[j], -(a.i * Bi[j])), fma(a.r, Bi[j], a.i * Br[j])});
       }
     }
     __syncthreads();
-    fft_dit_inv<false>(xs, P, tl);
+    fft_dit_inv<false, T>(xs, P, tl, t);
 #pragma unroll
     for (int j = 0; j < kCapKappa; ++j) {
-      const int64_t kap = t + (int64_t)j * kFftThreads;
+      const int64_t kap = t + (int64_t)j * T;
       if (kap < i) {
         const cplx c = fft_get<false>(xs, (int)kap);
         const double cr = c.r * inv_p, ci = c.i * inv_p;
@@ -552,11 +579,10 @@ k_cap_bluestein(int64_t nside, int64_t mmax, const double* map, const double* ft
     }
     __syncthreads();
   }
-  // Radix-4 step: Z_{kappa + s i} = sum_r (-i)^{rs} E_r(kappa).
-#pragma unroll
-  for (int j = 0; j < kCapKappa; ++j) {
-    const int64_t kap = t + (int64_t)j * kFftThreads;
-    if (kap < i) {
+  // Radix-4 step: Z_{kappa + s i} = sum_r (-i)^{rs} E_r(kappa).  (The
+  // barrier above orders the other wavefronts' E_r.)
+  for (int64_t kap = threadIdx.x; kap < i; kap += blockDim.x) {
+    {
       double Er[4], Ei[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -578,21 +604,40 @@ k_cap_bluestein(int64_t nside, int64_t mmax, const double* map, const double* ft
     }
   }
   __syncthreads();
-  double* fn = F + 2 * (i - 1) * (mmax + 1);
-  double* fs = F + 2 * (4 * N - i - 1) * (mmax + 1);
+  double* fn = F + 2 * (rn - 1) * (mmax + 1);
+  double* fs = F + 2 * (4 * N - rn - 1) * (mmax + 1);
   const int Li = (int)L;
-  for (int m = t; m <= (int)mmax; m += kFftThreads) {
+  for (int m = threadIdx.x; m <= (int)mmax; m += blockDim.x) {
     const int k = (int)((unsigned)m % (unsigned)Li), k2 = k == 0 ? 0 : Li - k;
     const double zr = Z[2 * k], zi = Z[2 * k + 1], yr = Z[2 * k2], yi = Z[2 * k2 + 1];
     const double nr = 0.5 * (zr + yr), ni = 0.5 * (zi - yi);    // (Z_k + conj Z_{L-k}) / 2
     const double sr = 0.5 * (zi + yi), si = -0.5 * (zr - yr);   // (Z_k - conj Z_{L-k}) / (2i)
-    double sp, cp;
-    sincospi((double)((unsigned)m % (unsigned)(2 * Li)) / (double)L, &sp, &cp);   // e^{-i pi m/L}
+    double sp = 0.0, cp = 1.0;
+    if (ring.half)
+      sincospi((double)((unsigned)m % (unsigned)(2 * Li)) / (double)L, &sp, &cp);   // e^{-i pi m/L}
     fn[2 * m] = fma(nr, cp, ni * sp);
     fn[2 * m + 1] = fma(ni, cp, -(nr * sp));
-    fs[2 * m] = fma(sr, cp, si * sp);
-    fs[2 * m + 1] = fma(si, cp, -(sr * sp));
+    if (pair) {
+      fs[2 * m] = fma(sr, cp, si * sp);
+      fs[2 * m + 1] = fma(si, cp, -(sr * sp));
+    }
   }
+}
+
+// One workgroup of kThreads per ring pair ring0 + blockIdx.x; pairs of
+// i <= kThreads (transforms of at most 2 kThreads points) take the four D_r
+// side by side.  One launch serves both kinds, so that the short transforms
+// do not wait for a launch of their own.
+template <int kThreads, bool kQuadOnly>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_ring_chirp(int64_t nside, int64_t mmax, const double* map, const double* ftab, double* zslot,
+             double* F, int64_t ring0) {
+  extern __shared__ double sm[];   // quarter twiddle table, then P points (per D_r)
+  const int64_t rn = ring0 + blockIdx.x;
+  if (kQuadOnly || (rn < nside ? rn : nside) <= kThreads)
+    ring_chirp<kThreads / 4, true>(sm, nside, mmax, map, ftab, zslot, F, rn);
+  else if constexpr (!kQuadOnly)
+    ring_chirp<kThreads, false>(sm, nside, mmax, map, ftab, zslot, F, rn);
 }
 
 // Step 2a: the pieces of lambda_mm(z) = g[m] sin^m(theta) for the north
@@ -1062,7 +1107,7 @@ size_t map2alm_scratch_bytes(int64_t nside, int64_t lmax) {
   const int64_t size = (lmax + 1) * (lmax + 2) / 2;
   return sizeof(double) * (size_t)(2 * nring * M) + sizeof(double) * (size_t)(2 * npair) +
          sizeof(double) * (size_t)(2 * size) + sizeof(double) * (size_t)part_doubles(nside, lmax) +
-         sizeof(double) * (size_t)(2 * (4 * nside + 1)) + sizeof(double) * (size_t)(2 * kFftMaxP) +
+         sizeof(double) * (size_t)(2 * (4 * nside + 1)) + sizeof(double) * (size_t)(2 * kTwP) +
          sizeof(double) * (size_t)M + 8 * 256;
 }
 
@@ -1087,14 +1132,22 @@ hipError_t launch_map2alm(int64_t nside, int64_t lmax, const double* map, double
   double* tab = (double*)p;
   p += align(sizeof(double) * (size_t)(2 * (4 * nside + 1)));
   double* ftab = (double*)p;
-  p += align(sizeof(double) * (size_t)(2 * kFftMaxP));
+  p += align(sizeof(double) * (size_t)(2 * kTwP));
   double* gain = (double*)p;
   const int64_t mblocks = (lmax + 64) / 64;
   // Belt rings by FFT when their length 4N is a power of two whose half
-  // fits the LDS buffer; cap rings by the chirp transform when their
-  // convolutions fit it; every other ring by direct sums.
+  // fits the LDS buffer; cap rings, and the belt of other Nside, by the chirp
+  // transform when their convolutions fit it; every other ring by direct
+  // sums.  Those read each ring once per 64 values of m, so their cost grows
+  // with Nside * (lmax / 64) per ring pair, where the chirp transform's nine
+  // FFTs of up to 4 Nside points hardly do (whole call, direct sums against
+  // the chirp transform: 212 against 187 us at Nside 250, lmax 500; 4041
+  // against 1135 us at Nside 1000, lmax 2000).  Nside 4096, lmax 6000 took
+  // 225 ms, 200 of them in direct sums, before the transforms covered it:
+  // 27.7 ms (chirp 2.1, belt FFT 0.87).
   const bool fft = (nside & (nside - 1)) == 0 && 2 * nside <= kBeltMaxH;
-  const bool caps = nside >= 2 && nside - 1 <= kFftMaxP / 2;
+  const bool caps = nside >= 2 && 2 * nside <= kFftMaxP;
+  const bool chirp_belt = !fft && caps && nside * mblocks >= kChirpBeltMin;
   {
     SetupArgs a;
     a.nside = nside;
@@ -1114,20 +1167,47 @@ hipError_t launch_map2alm(int64_t nside, int64_t lmax, const double* map, double
     k_setup<<<dim3((unsigned)nb), dim3(256), 0, st>>>(a);
   }
   if (fft) {
-    k_ring_fft<<<dim3((unsigned)(2 * nside + 1)), dim3(kFftThreads),
-                 fft_lds_bytes(2 * nside), st>>>(nside, lmax, map, tab, ftab, F);
+    const dim3 grid((unsigned)(2 * nside + 1));
+    const size_t lds = fft_lds_bytes(2 * nside);
+    if (2 * nside <= 8 * 512) k_ring_fft<512><<<grid, 512, lds, st>>>(nside, lmax, map, tab, ftab, F);
+    else k_ring_fft<1024><<<grid, 1024, lds, st>>>(nside, lmax, map, tab, ftab, F);
   }
-  if (caps) {
-    int64_t P = 1;
-    while (P < 2 * (nside - 1) - 1) P <<= 1;
-    k_cap_bluestein<<<dim3((unsigned)(nside - 1)), dim3(kFftThreads),
-                      fft_lds_bytes(P), st>>>(nside, lmax, map, ftab, part, F);
+  // Ring pairs lo .. hi by the chirp transform: workgroups of 256 threads
+  // where every pair's four transforms fit side by side (Nside <= 256), else
+  // of 512 for pairs of i <= 2048 and of 1024 for the longest.
+  auto chirp = [&](int64_t lo, int64_t hi) {
+    auto lds = [&](int64_t threads, int64_t to) {
+      const int64_t i = std::min(to, nside), P = pow2_at_least(2 * i - 1);
+      const int64_t quad = 4 * pow2_at_least(2 * std::min(i, threads) - 1);
+      return fft_lds_bytes(i <= threads ? quad : std::max(P, quad));
+    };
+    auto grid = [&](int64_t to) { return dim3((unsigned)(to - lo + 1)); };
+    if (nside <= 256) {
+      k_ring_chirp<256, true><<<grid(hi), 256, lds(256, hi), st>>>(nside, lmax, map, ftab, part, F,
+                                                                  lo);
+      return;
+    }
+    const int64_t to = nside <= 2048 ? hi : std::min<int64_t>(hi, 2048);
+    if (lo <= to) {
+      k_ring_chirp<512, false><<<grid(to), 512, lds(512, to), st>>>(nside, lmax, map, ftab, part,
+                                                                   F, lo);
+      lo = to + 1;
+    }
+    if (lo <= hi)
+      k_ring_chirp<1024, false><<<grid(hi), 1024, lds(1024, hi), st>>>(nside, lmax, map, ftab,
+                                                                      part, F, lo);
+  };
+  if (caps) chirp(1, nside - 1);
+  if (chirp_belt) {
+    // As many belt pairs at a time as the region holds Z slots for.
+    const int64_t most = std::max<int64_t>(1, part_doubles(nside, lmax) / (8 * nside));
+    for (int64_t r = nside; r <= 2 * nside; r += most)
+      chirp(r, std::min(r + most - 1, 2 * nside));
   }
   // Rings left for the direct sums: none, the belt, or all (Nside 1 has no
-  // cap rings; a belt done by FFT implies Nside <= 2048, where the caps
-  // take the chirp transform).
+  // cap rings).
   const bool caps_done = caps || nside == 1;
-  if (!(fft && caps_done)) {
+  if (!((fft || chirp_belt) && caps_done)) {
     const int64_t lo = caps_done ? nside : 1, hi = caps_done ? 3 * nside : 4 * nside - 1;
     const int64_t dft_waves = (hi - lo + 1) * mblocks;
     k_ring_dft<<<dim3((unsigned)((dft_waves + 3) / 4)), dim3(256), 0, st>>>(nside, lmax, map, F,
