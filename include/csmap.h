@@ -153,10 +153,18 @@ typedef enum {
      * value (default 5e-3, about 0.1 rad) and above CSMAP_OPT_NEAR_W uses
      * the algebraically equal form built from the dot products n.P/R, n.X',
      * n.Xdot; a step with some pair below it and none below
-     * CSMAP_OPT_NEAR_W forms n - P/R in FP32.  Minimum 1e-6. */
+     * CSMAP_OPT_NEAR_W forms n - P/R in FP32.  Minimum 1e-6.
+     * With the defaults of CSMAP_OPT_PIX_PER_LANE and CSMAP_OPT_ACCUM, a
+     * NEAR_W of at most 1e-3, Nside >= 64 (256 with visibility rules) and
+     * Nside x segments >= 65536, render forms every pair of a tile in the tile's own frame on the matrix
+     * cores, to at least the dot-product form's accuracy at any distance
+     * beyond 1.5 tile radii of the tile's centre; closer segments and those
+     * within NEAR_W of some pixel take the FP64 difference, and FAR_W only
+     * decides which steps mid_steps counts. */
     CSMAP_OPT_FAR_W = 9,
     /* Rings per tile G of the ring-block tiling: 0 (default: 2 x pixels per
-     * lane, i.e. rows of 32 pixels) or a power of two in 1 .. 64. */
+     * lane, i.e. rows of 32 pixels, or 32 rows of 16 where render sums on the
+     * matrix cores, see CSMAP_OPT_FAR_W) or a power of two in 1 .. 64. */
     CSMAP_OPT_BLOCK_RINGS = 10
 } csmap_option;
 

@@ -50,6 +50,9 @@ hipError_t launch_map2alm(int64_t nside, int64_t lmax, const double* map, double
 hipError_t launch_alm2cl(int64_t lmax, const double* alm, double* cl, hipStream_t st);
 hipError_t launch_forward(bool fp64, int K, bool persistent, const FwdArgs& A, unsigned grid,
                           unsigned block, hipStream_t st);
+hipError_t launch_tile_frames(const FwdArgs& A, int64_t ntiles, TileFrame* out, hipStream_t st);
+hipError_t launch_forward_m(bool persistent, const FwdArgs& A, unsigned grid, hipStream_t st);
+int forward_m_blocks_per_cu();
 int forward_blocks_per_cu(bool fp64, bool frac, int K, unsigned block);
 hipError_t launch_pixtab(int64_t nside, int64_t npix, const double* dmap, float* tab32,
                          double* tab64, hipStream_t st);
@@ -149,14 +152,17 @@ struct csmap_sky {
   int planned_K = -1;
   int planned_tiling = -1;
   int planned_rings = -1;
+  bool planned_matrix = false;
+  bool tiles_ready = false, frames_ready = false;   // plan and d_rows; d_frames
   Tiling plan;
   DevBuf d_rows;     // ring-block row table (empty for strips)
+  DevBuf d_frames;   // tile frames (matrix-core forward)
   DevBuf d_boxes, d_blk_box, d_blk_count, d_blk_prefix, d_box_count, d_raw_off, d_blk_mask;
   DevBuf d_flat_off, d_flat_rec, d_flat_part;
   DevBuf d_udir;      // caller directions of csmap_render_dirs, x | y | z
   DevBuf d_part;      // partial tiles of record slices (render; held by a captured graph)
   DevBuf d_udir_part; // csmap_render_dirs: the same
-  DevBuf d_rec32, d_phat64, d_rec64, d_orig;
+  DevBuf d_rec32, d_recm, d_phat64, d_rec64, d_orig;
   DevBuf d_tile_ptr, d_tile_boxes, d_items, d_box_items;
   std::vector<int64_t> box_items_off;  // per box offset into d_box_items (+ end)
   int64_t nblk = 0;
@@ -228,8 +234,38 @@ int64_t tile_pixels(const csmap_sky* s) { return 64 * (int64_t)s->K; }
 // pixels lying on one ring.
 bool use_blocks(const csmap_sky* s) { return s->tiling != 1; }
 
-// Rings per ring-block tile: 2 K rows of 32 pixels unless set.
-int block_rings(const csmap_sky* s) { return s->block_rings > 0 ? s->block_rings : 2 * s->K; }
+// Whether render's FP32C pair sums run on the matrix cores (k_fwd32m): tiles
+// of 512 pixels, one reciprocal per four terms, and tiles small enough on the
+// sky that few segments are near one: a segment within 1.5 tile radii, or of
+// the FP64 threshold, takes the slow path, about ten times a fast step.
+// Against the vector kernel, kernel times of one box seen by every pixel, 500
+// to 200,000 segments: 0.45-1.0x at Nside 32; 0.7x (500 segments) to 1.2x at
+// 64; 1.1-1.6x at 128 and 256; 1.2-1.3x at 512 and 1024; 1.3x at 2048 (720 to
+// 553 ms, 50,000 segments).  With visibility rules, whose pixels look at the
+// boxes they see: 0.7-1.1x at Nside 64 and 128, 1.0-1.25x at 256, 1.15-1.5x at
+// 512 and 1024.
+constexpr int64_t kMatrixNside = 64, kMatrixNsideRules = 256;
+constexpr int64_t kMatrixWork = 64 * 1024;   // Nside x segments
+constexpr double kMatrixNearW = 1e-3;
+bool has_rules(const csmap_sky* s) {
+  for (const HostBox& h : s->boxes)
+    if (h.geom.vis != CSMAP_VIS_ALL) return true;
+  return false;
+}
+bool use_matrix(const csmap_sky* s) {
+  return s->form == CSMAP_FORM_FP32C && s->frac != 0 && s->K == 8 &&
+         s->near_w <= kMatrixNearW && s->nside >= kMatrixNside &&
+         s->nside * s->total_seg >= kMatrixWork &&
+         (s->nside >= kMatrixNsideRules || !has_rules(s));
+}
+
+// Rings per ring-block tile unless set: 2 K rows of 32 pixels, or 32 rows of
+// 16 on the matrix cores (rows of pixels are about 2.4 times as wide as rings
+// are apart on the belt, so that these tiles are the rounder ones: a radius of
+// 8 against 12.5 mrad at Nside 2048).
+int block_rings(const csmap_sky* s) {
+  return s->block_rings > 0 ? s->block_rings : (use_matrix(s) ? 32 : 2 * s->K);
+}
 
 // Record slices.  A launch of fewer wavefronts than the chip holds leaves it
 // idle, and on an uneven sky the tiles that see most records finish last, so
@@ -242,13 +278,14 @@ int block_rings(const csmap_sky* s) { return s->block_rings > 0 ? s->block_rings
 // segments, FP32C: 58.1 ms against 0.16 ms.
 constexpr double kSliceItems = 32768.0;
 constexpr double kSliceMinRecords = 64.0;
+constexpr double kSliceMinMatrix = 256.0;   // a fast step there is four times as short
 // Share of a healpix-cone box's segments that its cone keeps, for planning
 // (0.13 on the stacking grids); the kept counts are not known on the host.
 constexpr double kConeShare = 0.13;
 
-int32_t slices_of(double cost, double total) {
-  const double most = cost / kSliceMinRecords;
-  const double want = cost * kSliceItems / std::max(total, 1.0);
+int32_t slices_of(double cost, double total, double items, bool matrix) {
+  const double most = cost / (matrix ? kSliceMinMatrix : kSliceMinRecords);
+  const double want = cost * items / std::max(total, 1.0);
   if (want <= 1.25 || most < 2.0) return 1;
   return (int32_t)std::ceil(std::min({want, most, 32768.0}));
 }
@@ -257,10 +294,12 @@ double planned_records(const HostBox& h) {
   return (double)h.n * (h.cone_nside > 0 ? kConeShare : 1.0);
 }
 
+FwdArgs fwd_args(csmap_sky* s, double* map);
+
 // Rebuild descriptors, compaction tables, record storage and the tile plan.
 csmap_status prepare(csmap_sky* s) {
   if (!s->dirty && s->planned_K == s->K && s->planned_tiling == s->tiling &&
-      s->planned_rings == block_rings(s))
+      s->planned_rings == block_rings(s) && s->planned_matrix == use_matrix(s))
     return CSMAP_OK;
   const int64_t nbox = (int64_t)s->boxes.size();
   hipStream_t st = s->stream;
@@ -318,6 +357,8 @@ csmap_status prepare(csmap_sky* s) {
   HIPCHK(s, s->d_orig.ensure(sizeof(int32_t) * nrec), "alloc records");
   if (s->form == CSMAP_FORM_FP32C) {
     HIPCHK(s, s->d_rec32.ensure(sizeof(float) * kRec32 * nrec), "alloc records");
+    if (use_matrix(s))
+      HIPCHK(s, s->d_recm.ensure(sizeof(float) * kRecM * nrec), "alloc records");
     HIPCHK(s, s->d_phat64.ensure(sizeof(double) * 4 * nrec), "alloc records");
   } else {
     HIPCHK(s, s->d_rec64.ensure(sizeof(double) * kRec64 * nrec), "alloc records");
@@ -341,18 +382,23 @@ csmap_status prepare(csmap_sky* s) {
     HIPCHK(s, hipMemcpyAsync(s->d_blk_box.p, blk_box.data(), sizeof(int32_t) * s->nblk,
                              hipMemcpyHostToDevice, st), "upload blocks");
 
-  // Tile plan.
+  // Tile plan.  The tiles, their rows and frames follow from the tiling alone
+  // and are kept while it stays, whatever the boxes.
   std::vector<int64_t> rows;
-  if (use_blocks(s)) {
-    const int G = block_rings(s);
-    make_ring_blocks(s->nside, G, 64 * (int64_t)s->K / G, s->plan);
-    ring_block_rows(s->plan, rows);
-    HIPCHK(s, s->d_rows.ensure(sizeof(int64_t) * rows.size()), "alloc rows");
-    HIPCHK(s, hipMemcpyAsync(s->d_rows.p, rows.data(), sizeof(int64_t) * rows.size(),
-                             hipMemcpyHostToDevice, st), "upload rows");
-  } else {
-    make_strips(s->nside, tile_pixels(s), s->plan);
-    s->d_rows.release();
+  if (!s->tiles_ready || s->planned_K != s->K || s->planned_tiling != s->tiling ||
+      s->planned_rings != block_rings(s)) {
+    s->tiles_ready = s->frames_ready = false;
+    if (use_blocks(s)) {
+      const int G = block_rings(s);
+      make_ring_blocks(s->nside, G, 64 * (int64_t)s->K / G, s->plan);
+      ring_block_rows(s->plan, rows);
+      HIPCHK(s, s->d_rows.ensure(sizeof(int64_t) * rows.size()), "alloc rows");
+      HIPCHK(s, hipMemcpyAsync(s->d_rows.p, rows.data(), sizeof(int64_t) * rows.size(),
+                               hipMemcpyHostToDevice, st), "upload rows");
+    } else {
+      make_strips(s->nside, tile_pixels(s), s->plan);
+      s->d_rows.release();
+    }
   }
   s->ntiles = s->plan.ntiles;
   s->all_boxes = true;
@@ -393,12 +439,16 @@ csmap_status prepare(csmap_sky* s) {
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(),
                    [&](int32_t a, int32_t b) { return cost[a] > cost[b]; });
+  // A matrix-core item takes four wavefronts; tiles of skies with rules differ
+  // in cost per record too, so those get twice the items to level out.
+  const bool matrix = use_matrix(s);
+  const double items = !matrix ? kSliceItems : (s->all_boxes ? kSliceItems / 4 : kSliceItems / 2);
   std::vector<WorkItem> work, split;
   work.reserve(s->ntiles);
   int32_t slot = 0;
   s->max_slices = 1;
   for (int32_t t : order) {
-    const int32_t ns = slices_of(cost[t], total);
+    const int32_t ns = slices_of(cost[t], total, items, matrix);
     s->max_slices = std::max(s->max_slices, ns);
     for (int32_t k = 0; k < ns; ++k) work.push_back({t, k, ns, slot});
     if (ns == 1) continue;
@@ -427,12 +477,20 @@ csmap_status prepare(csmap_sky* s) {
   if (!bitems.empty())
     HIPCHK(s, hipMemcpyAsync(s->d_box_items.p, bitems.data(), sizeof(int32_t) * bitems.size(),
                              hipMemcpyHostToDevice, st), "upload items");
+  if (use_matrix(s) && !s->frames_ready) {
+    HIPCHK(s, s->d_frames.ensure(sizeof(TileFrame) * (size_t)s->ntiles), "alloc tile frames");
+    HIPCHK(s, launch_tile_frames(fwd_args(s, nullptr), s->ntiles, s->d_frames.as<TileFrame>(), st),
+           "tile frames");
+    s->frames_ready = true;
+  }
   // Host staging vectors go out of scope below: wait for the copies.
   HIPCHK(s, hipStreamSynchronize(st), "upload plan");
   s->dirty = false;
   s->planned_K = s->K;
   s->planned_tiling = s->tiling;
   s->planned_rings = block_rings(s);
+  s->planned_matrix = use_matrix(s);
+  s->tiles_ready = true;
   return CSMAP_OK;
 }
 
@@ -451,6 +509,7 @@ PreArgs pre_args(csmap_sky* s) {
   A.box_count = s->d_box_count.as<DevBoxCount>();
   if (s->form == CSMAP_FORM_FP32C) {
     A.rec32 = s->d_rec32.as<float>();
+    if (use_matrix(s)) A.recm = s->d_recm.as<float>();
   } else {
     A.rec64 = s->d_rec64.as<double>();
   }
@@ -478,10 +537,12 @@ FwdArgs fwd_args(csmap_sky* s, double* map) {
   A.nside = s->nside;
   A.npix = s->npix;
   A.eta0 = s->eta0;
+  A.frames = s->d_frames.as<TileFrame>();
   A.dirx = s->d_dir.as<double>();
   A.diry = A.dirx + s->npix;
   A.dirz = A.dirx + 2 * s->npix;
   A.rec32 = s->d_rec32.as<float>();
+  A.recm = s->d_recm.as<float>();
   A.phat64 = s->d_phat64.as<double>();
   A.rec64 = s->d_rec64.as<double>();
   A.near_w = (float)s->near_w;
@@ -514,6 +575,9 @@ csmap_status check_forward(const csmap_sky* s, const FwdArgs& A, int K) {
   } else if (t.blocks || t.tile_px != 64 * (int64_t)K) {
     return fail(CSMAP_E_STATE, "strip tiling does not match the launch");
   }
+  if (use_matrix(s) && (!s->planned_matrix ||
+                        s->d_frames.cap < sizeof(TileFrame) * (size_t)t.ntiles))
+    return fail(CSMAP_E_STATE, "tile frames do not match the tile plan");
   if (!A.items && !A.work && A.nitems > t.ntiles)
     return fail(CSMAP_E_STATE, "more work items than tiles");
   if (A.work && (A.nitems != s->nwork || A.nsplit_tiles != s->nsplit_tiles ||
@@ -527,17 +591,26 @@ unsigned persistent_grid(const csmap_sky* s) {
   (void)hipGetDevice(&dev);
   int cus = 256;
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  // Exactly the workgroups that are resident at once: every wavefront pulls
-  // tiles until the queue is empty.
-  int per_cu = forward_blocks_per_cu(s->form == CSMAP_FORM_FP64, s->frac != 0, s->K,
-                                     64u * (unsigned)s->waves);
+  // Exactly the workgroups that are resident at once: every wavefront (or
+  // workgroup, on the matrix cores) pulls tiles until the queue is empty.
+  int per_cu = use_matrix(s) ? forward_m_blocks_per_cu()
+                             : forward_blocks_per_cu(s->form == CSMAP_FORM_FP64, s->frac != 0,
+                                                     s->K, 64u * (unsigned)s->waves);
   if (per_cu <= 0) per_cu = 1;
   return (unsigned)std::max(1, cus * per_cu);
 }
 
+// The sky's pair sums over A's work items with its present settings.
+hipError_t sky_forward(const csmap_sky* s, bool persistent, const FwdArgs& A, hipStream_t st) {
+  const unsigned waves = (unsigned)s->waves;
+  const unsigned grid =
+      persistent ? persistent_grid(s) : (unsigned)((A.nitems + waves - 1) / waves);
+  if (use_matrix(s)) return launch_forward_m(persistent, A, grid, st);
+  return launch_forward(s->form == CSMAP_FORM_FP64, s->K, persistent, A, grid, 64u * waves, st);
+}
+
 // Enqueue the whole render on stream st (no synchronisation, no events).
 csmap_status enqueue_render(csmap_sky* s, double* map, hipStream_t st, bool with_events) {
-  const bool fp64 = s->form == CSMAP_FORM_FP64;
   const PreArgs P = pre_args(s);
   FwdArgs A = fwd_args(s, map);
   if (s->schedule == 1) {
@@ -556,7 +629,6 @@ csmap_status enqueue_render(csmap_sky* s, double* map, hipStream_t st, bool with
                                  (uint32_t*)(s->d_counters.as<unsigned long long>() + 2), st),
          "counter reset");
   if (with_events) HIPCHK(s, hipEventRecord(s->ev[1], st), "event");
-  const unsigned block = 64u * (unsigned)s->waves;
   if (s->schedule == 2) {
     HIPCHK(s, launch_fill(map, s->npix, 0.0, st), "map clear");
     A.accumulate = 1;
@@ -566,15 +638,12 @@ csmap_status enqueue_render(csmap_sky* s, double* map, hipStream_t st, bool with
       A.only_box = (int32_t)b;
       A.items = s->d_box_items.as<int32_t>() + s->box_items_off[b];
       A.nitems = n;
-      const unsigned grid = (unsigned)((n + s->waves - 1) / s->waves);
-      HIPCHK(s, launch_forward(fp64, s->K, false, A, grid, block, st), "forward launch");
+      HIPCHK(s, sky_forward(s, false, A, st), "forward launch");
     }
   } else if (s->schedule == 1) {
-    HIPCHK(s, launch_forward(fp64, s->K, true, A, persistent_grid(s), block, st),
-           "forward launch");
+    HIPCHK(s, sky_forward(s, true, A, st), "forward launch");
   } else {
-    const unsigned grid = (unsigned)((s->ntiles + s->waves - 1) / s->waves);
-    HIPCHK(s, launch_forward(fp64, s->K, false, A, grid, block, st), "forward launch");
+    HIPCHK(s, sky_forward(s, false, A, st), "forward launch");
   }
   if (with_events) HIPCHK(s, hipEventRecord(s->ev[2], st), "event");
   return CSMAP_OK;
@@ -642,8 +711,8 @@ csmap_status csmap_destroy_sky(csmap_sky* s) {
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
   DevBuf* bufs[] = {&s->raw, &s->d_boxes, &s->d_blk_box, &s->d_blk_count, &s->d_blk_prefix,
                     &s->d_blk_mask, &s->d_flat_off, &s->d_flat_rec, &s->d_udir, &s->d_flat_part,
-                    &s->d_part, &s->d_udir_part, &s->d_rows,
-                    &s->d_box_count, &s->d_raw_off, &s->d_rec32, &s->d_phat64, &s->d_rec64,
+                    &s->d_part, &s->d_udir_part, &s->d_rows, &s->d_frames,
+                    &s->d_box_count, &s->d_raw_off, &s->d_rec32, &s->d_recm, &s->d_phat64, &s->d_rec64,
                     &s->d_orig, &s->d_tile_ptr, &s->d_tile_boxes, &s->d_items,
                     &s->d_box_items, &s->d_counters, &s->d_pixtab32, &s->d_pix64,
                     &s->d_partial, &s->d_adj_items, &s->d_adjc, &s->d_dir};
@@ -1231,7 +1300,7 @@ csmap_status csmap_render_dirs(csmap_sky* s, int64_t n, const double* xyz, doubl
     // Every tile walks every box, so all tiles take the same slices.
     double records = 0.0;
     for (const HostBox& h : s->boxes) records += planned_records(h);
-    A.nsplit = slices_of(records, records * (double)ntiles);
+    A.nsplit = slices_of(records, records * (double)ntiles, kSliceItems, false);
     A.nitems = ntiles * A.nsplit;
     if (A.nitems > INT32_MAX) return fail(CSMAP_E_STATE, "too many work items");
     if (A.nsplit > 1)
@@ -1594,15 +1663,13 @@ csmap_status csmap_autotune(csmap_sky* s, const char* cache_path) {
       return CSMAP_OK;
     }
     if (r != CSMAP_OK) return r;
-    const unsigned block = 64u * (unsigned)c.W;
-    const unsigned grid = c.S ? persistent_grid(s) : (unsigned)((A.nitems + c.W - 1) / c.W);
     double ms_min = 1e300;
     unsigned long long ctr[5] = {0, 0, 0, 0, 0};
     for (int rep = 0; rep < 3; ++rep) {
       HIPCHK(s, launch_zero_counters(s->d_counters.as<unsigned long long>(), 5, A.work_counter, st),
              "counter reset");
       HIPCHK(s, hipEventRecord(s->ev[0], st), "event");
-      HIPCHK(s, launch_forward(fp64, c.K, c.S == 1, A, grid, block, st), "forward launch");
+      HIPCHK(s, sky_forward(s, c.S == 1, A, st), "forward launch");
       HIPCHK(s, hipEventRecord(s->ev[1], st), "event");
       HIPCHK(s, hipEventSynchronize(s->ev[1]), "sync");
       float ms = 0.f;

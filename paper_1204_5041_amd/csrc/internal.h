@@ -58,6 +58,15 @@ struct DevBoxCount {
 //           (1 - |Xdot| < 0.05), else 0
 //   [14..15] unused
 constexpr int kRec32 = 16;
+// Matrix-core record of the same segment: 12 floats.  With k = |kappa| and
+// h = sqrt(k) (P/R).T / 2,
+//   [0..2]  k V,           [3] 1 + (P/R).V
+//   [4..6]  sqrt(k) T,     [7] h
+//   [8]     h^2,           [9] 1/k (0 if k is 0)
+//   [10]    sign of w's row: -1 if kappa < 0, else 1
+//   [11]    1 if the segment must take the FP64 path (the flag of [13] above,
+//           or k outside 2^-100 .. 2^100 and not 0), else 0
+constexpr int kRecM = 12;
 // FP64 record: 16 doubles.
 //   [0..2] P/R rounded (hi), [3..5] X', [6..8] Xdot, [9] -4 eps dsigma / R,
 //   [10] index of the segment inside its box, [11] R,
@@ -81,6 +90,7 @@ struct PreArgs {
   DevBoxCount* box_count;
   float* rec32;                // FP32C records (or null)
   double* phat64;              // FP32C: P/R in FP64, 4 doubles per record
+  float* recm;                 // matrix-core records (or null)
   double* rec64;               // FP64 records (or null)
   int32_t* orig_index;         // record -> index of the segment in its box
   // Adjoint only (or null): per record the FP32C constants per unit dsigma,
@@ -113,6 +123,16 @@ struct FlatArgs {
 };
 constexpr int kFlatRec = 8;
 
+// Frame of a tile of the forward launch: its centre c (the normalised mean of
+// its pixel directions), tangent axes e1 and e2, and the largest angle rho of
+// a pixel from c.
+struct TileFrame {
+  double c[3];
+  double e1[3], e2[3];
+  float axis[3][3];   // e1, e2, c rounded
+  float rho;
+};
+
 // A unit of forward work: slice `slice` of the `slices` into which the records
 // seen by a tile are cut (box_records).  With one slice the tile's sums go to
 // the map; otherwise to partial tile slot + slice (64 K doubles, pixel slot j
@@ -137,10 +157,12 @@ struct FwdArgs {
   uint32_t* work_counter;      // persistent schedule: next item
   int64_t nside, npix;
   double eta0;
+  const TileFrame* frames;     // tile frames (k_fwd32m)
   const double* dirx;          // pixel direction table (RING order, FP64)
   const double* diry;
   const double* dirz;
   const float* rec32;
+  const float* recm;
   const double* phat64;
   const double* rec64;
   float near_w;                // FP32C: pairs with 1 - n.Ph below this take the FP64 difference

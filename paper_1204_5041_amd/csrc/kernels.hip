@@ -340,6 +340,18 @@ __device__ __forceinline__ void emit_record(const PreArgs& A, const DevBox& bx, 
     const double vv = (g.V[0] * g.V[0] + g.V[1] * g.V[1]) + g.V[2] * g.V[2];
     const float force_near = (1.0 - sqrt(vv) < 0.05) ? 1.0f : 0.0f;
     o[3] = make_float4(__int_as_float((int)i), force_near, 0.f, 0.f);
+    if (A.recm) {
+      const double k = fabs(kh), root = sqrt(k), h = 0.5 * root * pt;
+      // Beyond these bounds parts of the split rows leave FP32's exponents.
+      const bool odd = !(k < 0x1p100) || (k < 0x1p-100 && k != 0.0);
+      float4* m = (float4*)(A.recm + (size_t)r * kRecM);
+      m[0] = make_float4((float)(k * g.V[0]), (float)(k * g.V[1]), (float)(k * g.V[2]),
+                         (float)(1.0 + pv));
+      m[1] = make_float4((float)(root * g.T[0]), (float)(root * g.T[1]), (float)(root * g.T[2]),
+                         (float)h);
+      m[2] = make_float4((float)(h * h), k != 0.0 ? (float)(1.0 / k) : 0.f,
+                         kh < 0.0 ? -1.f : 1.f, (odd || force_near != 0.f) ? 1.f : 0.f);
+    }
     if (A.adjc) {
       // The adjoint's constants, without kappa (every adjoint sum is linear
       // in kappa, which the finalize step applies in FP64).
@@ -1072,6 +1084,441 @@ __global__ void __launch_bounds__(256) k_fwd32(FwdArgs A) {
   if (lane == 0 && all_steps) atomicAdd(A.steps, all_steps);
 }
 
+// ---------------------------------------------------------------------------
+// Forward, FP32C form, on the matrix cores.
+//
+// In the frame of a tile (centre c, tangent axes e1, e2) a pixel is
+// n' = n - c = (x1, x2, x3), x3 = c.n - 1 = -|n'|^2/2, and a segment
+// d = Ph - c.  The three forms a pair needs are affine in n':
+//   w   = 1 - n.Ph = |n' - d|^2/2 = -n'.d - x3 + |d|^2/2,
+//   v   = Xdot.(n - Ph)           =  Xdot.n' - Xdot.d,
+//   u   = X'.(n - Ph)             =  X'.n'   - X'.d,
+// three products of a row of four numbers per segment with a column
+// (x1, x2, x3, 1) per pixel.  The term is kappa' m/(b w) with b = 1 + n.Xdot =
+// v + b0, a = n.X' = u + a0 (b0 = 1 + Ph.Xdot, a0 = Ph.X') and m = v b - u a =
+// v b - (u + a0/2)^2 + a0^2/4.  With k = |kappa'| the rows carry k v,
+// y = sqrt(k) (u + a0/2) and -w (w where kappa' > 0), so that a pair takes
+// b = (k v)/k + b0, k m = (k v) b + k a0^2/4 - y^2 and b w: four operations.
+// Every number in a row or column is of the size it has in
+// the tile, so that w and the differences keep FP32's relative accuracy down
+// to angles of 1.5 tile radii from the centre, where the error of w is at
+// most about 3 (theta + rho)^2/(theta - rho)^2 2^-24 <= 4.5e-6 (the far form
+// of the vector kernel: 1.2e-5 at its threshold).
+//
+// The products run on the bf16 matrix cores without losing FP32's 24 bits:
+// each number is split into three bf16 parts (8 bits each, exact), and the
+// eight partial products above 2^-32 of the whole (parts (0,0), (0,1),
+// (1,0), (1,1), (0,2), (2,0), (1,2), (2,1)) take eight of the instruction's
+// 32 terms for each component, the constant's three parts three more.  They
+// are summed in FP32 inside one v_mfma_f32_16x16x32_bf16: measured against
+// 64 bits its error is 2.9e-8 rms, 1.1e-7 at most, of the summed magnitudes
+// (the FP32 FMA chain: 3.3e-8 and 1.4e-7).  The FP32 matrix instruction
+// would take twice the cycles.
+//
+// A workgroup of four wavefronts owns a tile of 512 pixels, 128 per
+// wavefront: eight columns of 16 pixels, so that a 16 x 16 result leaves a
+// lane four segments of one pixel, whose terms are folded into one fraction
+// and divided once; the four lane groups hold partial sums of the same
+// pixels, added at the end.  The rows of 64 segments at a time are formed by
+// the whole workgroup (wavefront role g: component g of the lane's segment)
+// and shared through LDS, one block ahead.  Segments closer than the limit
+// above (and those flagged at precompute) get neutral rows there and go
+// through the FP64 difference one by one, two pixels per lane.
+//
+// It is bound by instruction issue: per 256 pairs three matrix instructions
+// (16 cycles each) and 27 vector ones with the reciprocal (60 cycles), which
+// overlap hardly at all (interleaving them one to nine measured the same).
+// One box of 50,000 segments at Nside 2048: 553 ms (4.55e12 pairs/s) against
+// 720 ms on the vector kernel; 514 ms without staging the rows.
+// ---------------------------------------------------------------------------
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int kMTile = 512;     // pixels of a tile
+constexpr int kMCols = 8;       // 16-pixel columns per wavefront
+constexpr int kMRows = 64;      // segments per LDS block
+constexpr float kMReach = 1.5f; // closest segment, in tile radii from the centre
+
+typedef const TileFrame __attribute__((address_space(4)))* cframe_p;
+
+struct MBlock {
+  bf16x8 a[3][kMRows / 16][64];   // rows of w, v, u: [form][segment / 16][lane]
+  float b0[kMRows], hh[kMRows], g[kMRows];
+  unsigned long long near, mid;   // segments for the FP64 path; below far_w (counted)
+};
+
+__device__ __forceinline__ void split_bf16(float x, __bf16& p0, __bf16& p1, __bf16& p2) {
+  p0 = (__bf16)x;
+  const float r = x - (float)p0;
+  p1 = (__bf16)r;
+  p2 = (__bf16)(r - (float)p1);
+}
+
+__device__ __forceinline__ bf16x8 row_parts(float y, bool constant) {
+  __bf16 a, b, c;
+  split_bf16(y, a, b, c);
+  const __bf16 z = (__bf16)0.0f;
+  return constant ? bf16x8{a, b, c, z, z, z, z, z} : bf16x8{a, b, a, b, c, a, c, b};
+}
+
+__device__ __forceinline__ bf16x8 column_parts(float x, bool constant) {
+  __bf16 a, b, c;
+  split_bf16(x, a, b, c);
+  const __bf16 z = (__bf16)0.0f, o = (__bf16)1.0f;
+  return constant ? bf16x8{o, o, o, z, z, z, z, z} : bf16x8{a, a, b, b, a, c, b, c};
+}
+
+// 2 sin^2(x/2) = 1 - cos x for an angle x, 2 from pi on.
+__device__ __forceinline__ float versine(float x) {
+  if (x >= 3.14159f) return 2.0f;
+  const float s = sinf(0.5f * x);
+  return 2.0f * s * s;
+}
+
+// One frame per tile: wavefront per tile, lane l taking slots 64 j + l.
+template <int K>
+__global__ void __launch_bounds__(256) k_tile_frames(FwdArgs A, int64_t ntiles, TileFrame* out) {
+  const int lane = threadIdx.x & 63;
+  const int64_t t = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (t >= ntiles) return;
+  const LaneRow lr = lane_row<K>(A, t, lane);
+  double n[K][3], c[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const int64_t p = lr.first + slot_off(lr, j);
+    n[j][0] = A.dirx[p];
+    n[j][1] = A.diry[p];
+    n[j][2] = A.dirz[p];
+    const double in = lr.pos0 + j * lr.step < lr.cnt ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c[k] += in * n[j][k];
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c[k] += __shfl_xor(c[k], off);
+  double r = sqrt((c[0] * c[0] + c[1] * c[1]) + c[2] * c[2]);
+  if (!(r > 1e-6)) {   // a tile around the whole sky has no centre: any will do
+    c[0] = c[1] = 0.0;
+    c[2] = r = 1.0;
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) c[k] /= r;
+  double far = 0.0;   // largest |n - c|^2
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const double x = n[j][0] - c[0], y = n[j][1] - c[1], z = n[j][2] - c[2];
+    if (lr.pos0 + j * lr.step < lr.cnt) far = fmax(far, (x * x + y * y) + z * z);
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) far = fmax(far, __shfl_xor(far, off));
+  if (lane != 0) return;
+  TileFrame f;
+  const bool polar = fabs(c[2]) > 0.9;
+  const double h = polar ? sqrt(c[1] * c[1] + c[2] * c[2]) : sqrt(c[0] * c[0] + c[1] * c[1]);
+  f.e1[0] = polar ? 0.0 : -c[1] / h;
+  f.e1[1] = polar ? -c[2] / h : c[0] / h;
+  f.e1[2] = polar ? c[1] / h : 0.0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    f.c[k] = c[k];
+    f.e2[k] = c[(k + 1) % 3] * f.e1[(k + 2) % 3] - c[(k + 2) % 3] * f.e1[(k + 1) % 3];
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    f.axis[0][k] = (float)f.e1[k];
+    f.axis[1][k] = (float)f.e2[k];
+    f.axis[2][k] = (float)c[k];
+  }
+  f.rho = 1.000001f * (float)(2.0 * asin(fmin(1.0, 0.5 * sqrt(far))));
+  out[t] = f;
+}
+
+// The rows of one block: records r0 + lane, the first n of them real, by the
+// wavefront of role g (0, 1, 2: component along the axis; 3: the constants).
+__device__ __forceinline__ void stage_rows(const FwdArgs& A, MBlock& sh, int lane, int role,
+                                           cframe_p fr, float t_near, float t_mid, int64_t r0,
+                                           int32_t n) {
+  const int64_t r = r0 + (lane < n ? lane : n - 1);
+  const float4* M = (const float4*)(A.recm + (size_t)r * kRecM);
+  const float4 mv = M[0], mt = M[1], mk = M[2];
+  const double2 h0 = ((const double2*)A.phat64)[2 * r];
+  const double pz = A.phat64[4 * r + 2];
+  const float dx = (float)(h0.x - fr->c[0]), dy = (float)(h0.y - fr->c[1]);
+  const float dz = (float)(pz - fr->c[2]);
+  const float t = 0.5f * fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+  const bool real = lane < n;
+  const bool near = real && (!(t >= t_near) || mk.w != 0.f);
+  const bool neutral = !real || near;   // m = 0 and b w = 1 for every pixel
+  bf16x8* const to = &sh.a[0][lane >> 4][role * 16 + (lane & 15)];
+  constexpr int kForm = kMRows / 16 * 64;   // rows of the next form
+  if (role < 3) {
+    const float ex = fr->axis[role][0], ey = fr->axis[role][1], ez = fr->axis[role][2];
+    const float dd = fmaf(ez, dz, fmaf(ey, dy, ex * dx));
+    const float one = role == 2 ? -1.0f : 0.0f;
+    const float yw = (one - dd) * mk.z;
+    const float yv = fmaf(ez, mv.z, fmaf(ey, mv.y, ex * mv.x));
+    const float yu = fmaf(ez, mt.z, fmaf(ey, mt.y, ex * mt.x));
+    to[0] = row_parts(neutral ? 0.f : yw, false);
+    to[kForm] = row_parts(neutral ? 0.f : yv, false);
+    to[2 * kForm] = row_parts(neutral ? 0.f : yu, false);
+  } else {
+    const float yv = -fmaf(dz, mv.z, fmaf(dy, mv.y, dx * mv.x));
+    const float yu = mt.w - fmaf(dz, mt.z, fmaf(dy, mt.y, dx * mt.x));
+    to[0] = row_parts(neutral ? 1.f : t * mk.z, true);
+    to[kForm] = row_parts(neutral ? 0.f : yv, true);
+    to[2 * kForm] = row_parts(neutral ? 0.f : yu, true);
+    sh.b0[lane] = neutral ? 1.f : mv.w;
+    sh.hh[lane] = neutral ? 0.f : mk.x;
+    sh.g[lane] = neutral ? 0.f : mk.y;
+    const unsigned long long nm = __ballot(near), mm = __ballot(real && !near && t < t_mid);
+    if (lane == 0) {
+      sh.near = nm;
+      sh.mid = mm;
+    }
+  }
+}
+
+template <bool PERSISTENT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_fwd32m(FwdArgs A) {
+  __shared__ MBlock sh[2];
+  __shared__ uint32_t next;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = lane >> 4, col = lane & 15;
+  unsigned long long near_steps = 0, mid_steps = 0, all_steps = 0, pairs = 0;
+  const cf4p recs = (cf4p)A.rec32;
+  const cd2p ph64 = (cd2p)A.phat64;
+  int64_t item = blockIdx.x;
+  while (true) {
+    if constexpr (PERSISTENT) {
+      if (threadIdx.x == 0) next = atomicAdd(A.work_counter, 1u);
+      __syncthreads();
+      item = __builtin_amdgcn_readfirstlane(next);
+      __syncthreads();
+    }
+    if (item >= A.nitems) break;
+    const WorkItem wi = work_item(A, item);
+    const int64_t tile = wi.tile;
+    const cframe_p fr = (cframe_p)A.frames + tile;   // scalar loads
+    const double c0 = fr->c[0], c1 = fr->c[1], c2 = fr->c[2];
+    const float rho = fr->rho;
+    const float t_near = versine(fmaxf(kMReach * rho, rho + acosf(fmaxf(-1.0f, 1.0f - A.near_w))));
+    const float t_mid = versine(rho + acosf(fmaxf(-1.0f, 1.0f - A.far_w)));
+    // Pixel slot s of the tile: position s % W of row s / W, W = 512 / rings.
+    const int wshift = 3 + A.ring_shift;   // log2 W (64 / rings lanes of 8 slots)
+    // This lane's pixels 16 (grp + 4 h) + col, h = 0, 1, of its wavefront:
+    // written, tested for visibility and summed by the FP64 path.
+    auto slot_pixel = [&](int s, bool& in, int64_t& p) {
+      int64_t first;
+      int32_t cnt, pos;
+      if (A.rows) {
+        const int64_t e = A.rows[tile * A.ring_g + (s >> wshift)];
+        first = e >> kRowCountBits;
+        cnt = (int32_t)(e & ((1 << kRowCountBits) - 1));
+        pos = s & ((1 << wshift) - 1);
+      } else {
+        first = tile * kMTile;
+        const int64_t room = A.npix - first;
+        cnt = room >= kMTile ? kMTile : (room > 0 ? (int32_t)room : 0);
+        if (cnt == 0) first = 0;
+        pos = s;
+      }
+      in = pos < cnt;
+      p = first + (in ? pos : (cnt > 0 ? cnt - 1 : 0));
+    };
+    bool in2[2];
+    int32_t p2[2];   // pixel indices are below 2^30
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      int64_t p;
+      slot_pixel(wave * 128 + 16 * (grp + 4 * h) + col, in2[h], p);
+      p2[h] = (int32_t)p;
+    }
+    // Columns: component grp of each pixel's n'.
+    bf16x8 B[kMCols];
+    {
+      const double a0 = grp == 0 ? fr->e1[0] : (grp == 1 ? fr->e2[0] : c0);
+      const double a1 = grp == 0 ? fr->e1[1] : (grp == 1 ? fr->e2[1] : c1);
+      const double a2 = grp == 0 ? fr->e1[2] : (grp == 1 ? fr->e2[2] : c2);
+#pragma unroll
+      for (int j = 0; j < kMCols; ++j) {
+        bool in;
+        int64_t p;
+        slot_pixel(wave * 128 + 16 * j + col, in, p);
+        const double x = (a0 * (A.dirx[p] - c0) + a1 * (A.diry[p] - c1)) + a2 * (A.dirz[p] - c2);
+        B[j] = column_parts((float)x, grp == 3);
+      }
+    }
+    float S[kMCols], C[kMCols], part[kMCols];
+#pragma unroll
+    for (int j = 0; j < kMCols; ++j) S[j] = C[j] = part[j] = 0.f;
+    int32_t b0 = 0, b1 = A.nbox;
+    if (A.only_box >= 0) { b0 = A.only_box; b1 = A.only_box + 1; }
+    else if (!A.all_boxes) { b0 = ((ci32p)A.tile_ptr)[tile]; b1 = ((ci32p)A.tile_ptr)[tile + 1]; }
+    const bool list = !A.all_boxes && A.only_box < 0;
+    SliceRange sr = slice_range(A, wi, list, b0, b1, lane);
+    int buf = 0;
+    for (int32_t bi = sr.bi; bi < b1 && sr.pos < sr.hi; ++bi) {
+      const int32_t b = list ? ((ci32p)A.tile_boxes)[bi] : bi;
+      int64_t r0, r1;
+      box_records(A, b, sr, r0, r1);
+      if (r1 <= r0) continue;
+      // Visibility of the wavefront's 128 pixels, two per lane, as masks.
+      unsigned long long vis[2];
+      {
+        const DevBox bx = load_box(A.boxes, b);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          bool v = in2[h];
+          if (bx.vis != 0) v = v && sees_box(A.dirx[p2[h]], A.diry[p2[h]], A.dirz[p2[h]], bx, A.eta0);
+          vis[h] = __ballot(v);
+        }
+        const int any = __popcll(vis[0]) + __popcll(vis[1]);
+        if (bx.vis != 0 && !__syncthreads_or(any)) continue;
+        if (any) {
+          pairs += (unsigned long long)any * (unsigned long long)(r1 - r0);
+          all_steps += (unsigned long long)(r1 - r0);
+        }
+      }
+      const bool sees = (vis[0] | vis[1]) != 0;
+      const int32_t nrec = (int32_t)(r1 - r0), nblk = (nrec + kMRows - 1) / kMRows;
+      auto stage = [&](int32_t k, MBlock& to) {
+        // Roles move on with the block, so that no SIMD always gets the same.
+        const int role = (wave + k) & 3;
+        const int32_t left = nrec - k * kMRows;
+        stage_rows(A, to, lane, role, fr, t_near, t_mid, r0 + (int64_t)k * kMRows,
+                   left < kMRows ? left : kMRows);
+      };
+      int32_t terms = 0;
+      stage(0, sh[buf]);
+      __syncthreads();
+      for (int32_t k = 0; k < nblk; ++k) {
+        if (k + 1 < nblk) stage(k + 1, sh[buf ^ 1]);
+        const MBlock& m = sh[buf];
+        if (sees) {
+          const int32_t left = nrec - k * kMRows;
+          const int nrt = left < kMRows ? (left + 15) >> 4 : kMRows / 16;
+#pragma unroll 1
+          for (int rt = 0; rt < nrt; ++rt) {
+            const bf16x8 aw = m.a[0][rt][lane], av = m.a[1][rt][lane], au = m.a[2][rt][lane];
+            const f32x4 kb = *(const f32x4*)&m.b0[16 * rt + 4 * grp];
+            const f32x4 ka = *(const f32x4*)&m.hh[16 * rt + 4 * grp];
+            const f32x4 kg = *(const f32x4*)&m.g[16 * rt + 4 * grp];
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < kMCols; ++j) {
+              const f32x4 w = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw, B[j], zero, 0, 0, 0);
+              const f32x4 v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, B[j], zero, 0, 0, 0);
+              const f32x4 u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(au, B[j], zero, 0, 0, 0);
+              float n[4], d[4];
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                const float bb = fmaf(v[q], kg[q], kb[q]);
+                n[q] = fmaf(-u[q], u[q], fmaf(v[q], bb, ka[q]));
+                d[q] = bb * w[q];
+              }
+              const float n01 = fmaf(n[0], d[1], n[1] * d[0]), d01 = d[0] * d[1];
+              const float n23 = fmaf(n[2], d[3], n[3] * d[2]), d23 = d[2] * d[3];
+              part[j] = fmaf(fmaf(n01, d23, n23 * d01), __builtin_amdgcn_rcpf(d01 * d23), part[j]);
+            }
+          }
+          mid_steps += __popcll(m.mid);
+          // Close segments, in order: the terms of pixels (grp + 4 h, col)
+          // go to this lane's partial sums of those columns.  The next
+          // segment's record is requested before this one is used.
+          unsigned long long todo = (unsigned long long)uniform_i64((int64_t)m.near);
+          if (todo) {
+            near_steps += __popcll(todo);
+            double nd[2][3];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              nd[h][0] = A.dirx[p2[h]];
+              nd[h][1] = A.diry[p2[h]];
+              nd[h][2] = A.dirz[p2[h]];
+            }
+            const int64_t rk = r0 + (int64_t)k * kMRows;
+            int64_t r = rk + __builtin_ctzll(todo);
+            v4f q0 = recs[4 * r], q1 = recs[4 * r + 1], q2 = recs[4 * r + 2];
+            v2d h0 = ph64[2 * r], h1 = ph64[2 * r + 1];
+            while (todo) {
+              todo &= todo - 1;
+              if (todo) r = rk + __builtin_ctzll(todo);
+              __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this record has arrived
+              const v4f n0 = recs[4 * r], n1 = recs[4 * r + 1], n2 = recs[4 * r + 2];
+              const v2d g0 = ph64[2 * r], g1 = ph64[2 * r + 1];
+              float term[2];
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                const float fx = (float)nd[h][0], fy = (float)nd[h][1], fz = (float)nd[h][2];
+                const float dx = (float)(nd[h][0] - h0.x), dy = (float)(nd[h][1] - h0.y);
+                const float dz = (float)(nd[h][2] - h1.x);
+                const float a = fmaf(fz, q1.y, fmaf(fy, q1.x, fx * q0.w));
+                const float bb = fmaf(fz, q2.x, fmaf(fy, q1.w, fmaf(fx, q1.z, 1.0f)));
+                const float q = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                const float t1 = q2.y * fmaf(q2.x, dz, fmaf(q1.w, dy, q1.z * dx));
+                const float t2 = q2.y * fmaf(q1.y, dz, fmaf(q1.x, dy, q0.w * dx));
+                const float mm = fmaf(-a, t2, t1 * bb);
+                term[h] = mm * __builtin_amdgcn_rcpf(bb * fmaxf(0.5f * q, 1e-30f));
+              }
+#pragma unroll
+              for (int j = 0; j < kMCols; ++j) part[j] += grp == (j & 3) ? term[j >> 2] : 0.0f;
+              q0 = n0;
+              q1 = n1;
+              q2 = n2;
+              h0 = g0;
+              h1 = g1;
+            }
+          }
+          terms += kMRows / 4;
+          if (terms >= A.chunk || k + 1 == nblk) {
+#pragma unroll
+            for (int j = 0; j < kMCols; ++j) {
+              const bool v = (vis[j >> 2] >> (16 * (j & 3) + col)) & 1;
+              kahan_add(S[j], C[j], v ? part[j] : 0.0f);
+              part[j] = 0.f;
+            }
+            terms = 0;
+          }
+        }
+        __syncthreads();
+        buf ^= 1;
+      }
+    }
+    // The four lane groups' sums of each pixel, then lane group j mod 4
+    // writes column j.
+    double out[2] = {0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < kMCols; ++j) {
+      double v = (double)S[j] - (double)C[j];
+      v += __shfl_xor(v, 16);
+      v += __shfl_xor(v, 32);
+      if (grp == (j & 3)) out[j >> 2] = v;
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (!in2[h]) continue;
+      if (wi.slices > 1) {
+        // The partial tile's layout: row's lane and its slot (lane_row).
+        const int s = wave * 128 + 16 * (grp + 4 * h) + col;
+        const int row = A.rows ? s >> wshift : 0, pos = A.rows ? s & ((1 << wshift) - 1) : s;
+        const int ln = (row << A.ring_shift) + (pos & ((1 << A.ring_shift) - 1));
+        A.part[(int64_t)(wi.slot + wi.slice) * kMTile + 64 * (pos >> A.ring_shift) + ln] = out[h];
+      } else {
+        A.map[p2[h]] = A.accumulate ? A.map[p2[h]] + out[h] : out[h];
+      }
+    }
+    if constexpr (!PERSISTENT) {
+      item += gridDim.x;
+    }
+  }
+  if (lane == 0 && pairs) atomicAdd(A.pairs, pairs);
+  if (lane == 0 && near_steps) atomicAdd(A.near_steps, near_steps);
+  if (lane == 0 && mid_steps) atomicAdd(A.mid_steps, mid_steps);
+  if (lane == 0 && all_steps) atomicAdd(A.steps, all_steps);
+}
+
 __device__ __forceinline__ double rcp_f64(double x) {
   // The hardware estimate r (relative error e = 1 - x r below 2^-24)
   // refined by one third-order step: 1/x = r / (1 - e) = r (1 + e + e^2 +
@@ -1652,6 +2099,30 @@ int forward_blocks_per_cu(bool fp64, bool frac, int K, unsigned block) {
   return 0;
 }
 
+// Frames of the ntiles tiles of A's tiling (K = 8).
+hipError_t launch_tile_frames(const FwdArgs& A, int64_t ntiles, TileFrame* out, hipStream_t st) {
+  if (ntiles > 0)
+    k_tile_frames<8><<<dim3((unsigned)((ntiles + 3) / 4)), dim3(256), 0, st>>>(A, ntiles, out);
+  return hipGetLastError();
+}
+
+// Workgroups of the persistent matrix-core forward kernel on one CU.
+int forward_m_blocks_per_cu() {
+  int nb = 0;
+  const hipError_t e =
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fwd32m<true>, 256, 0);
+  return e == hipSuccess ? nb : 0;
+}
+
+static hipError_t launch_combine(int K, const FwdArgs& A, hipStream_t st);
+
+// One workgroup per work item, or the persistent grid of `grid` workgroups.
+hipError_t launch_forward_m(bool persistent, const FwdArgs& A, unsigned grid, hipStream_t st) {
+  if (persistent) k_fwd32m<true><<<dim3(grid), dim3(256), 0, st>>>(A);
+  else k_fwd32m<false><<<dim3((unsigned)A.nitems), dim3(256), 0, st>>>(A);
+  return launch_combine(8, A, st);
+}
+
 hipError_t launch_forward(bool fp64, int K, bool persistent, const FwdArgs& A, unsigned grid,
                           unsigned block, hipStream_t st) {
   switch (K) {
@@ -1665,6 +2136,10 @@ hipError_t launch_forward(bool fp64, int K, bool persistent, const FwdArgs& A, u
                        : fwd_launch<8, false>(fp64, A, grid, block, st); break;
     default: return hipErrorInvalidValue;
   }
+  return launch_combine(K, A, st);
+}
+
+static hipError_t launch_combine(int K, const FwdArgs& A, hipStream_t st) {
   const int64_t nt = A.split ? A.nsplit_tiles : (A.nsplit > 1 ? A.nitems / A.nsplit : 0);
   if (nt > 0) {
     // About eight slices (one round of loads) per wavefront, at most 16.
