@@ -74,3 +74,19 @@ def test_sliced_directions(B, form, n):
     assert sky.stats()["pairs"] == n * 733
     assert e["rel_rms"] <= rms and e["rel_max"] <= mx, e
     sky.close()
+
+
+@pytest.mark.parametrize("K", [1, 2, 4, 8])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 63, 64, 65, 67])
+def test_fp64_windows(B, K, n):
+    """Windows of four terms per division and their remainders, with exact
+    coincidences (Nside 1 pixel 4 is +x) filling a whole window."""
+    box = synth.make_box(n, 991, origin=(0.0, 0.0, 0.0), eta_lo=0.0, eta_hi=16.0)
+    box.x_rel[::2] = (0.5, 0.0, 0.0)
+    box.x_rel[:4] = (0.5, 0.0, 0.0)
+    w = synth.Workload("windows", 1, 16.0, [box])
+    ref = oracle.theta_pixels(1, np.arange(12), w.eta0, w.boxes)
+    sky = sky_from_workload(w, B.CSMAP_FORM_FP64, {B.CSMAP_OPT_PIX_PER_LANE: K})
+    e = err_metrics(sky.render().cpu().numpy(), ref)
+    assert e["rel_rms"] <= 1e-12 and e["rel_max"] <= 1e-12, e
+    sky.close()
