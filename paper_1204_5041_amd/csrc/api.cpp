@@ -56,12 +56,10 @@ int forward_m_blocks_per_cu();
 int forward_blocks_per_cu(bool fp64, bool frac, int K, unsigned block);
 hipError_t launch_pixtab(int64_t nside, int64_t npix, const double* dmap, float* tab32,
                          double* tab64, hipStream_t st);
+int adjoint_blocks_per_cu();
 hipError_t launch_adjoint(const AdjArgs& A, hipStream_t st);
-hipError_t launch_adj_finalize(const DevBox* boxes, const DevBoxCount* counts, int32_t b,
-                               int64_t nseg, const char* raw, const int32_t* orig_index,
-                               const double* phat64, const double* partial, int32_t nsplit,
-                               double* gx, double* gxd, double* gxp, double* gds,
-                               hipStream_t st);
+hipError_t launch_adj_finalize(const AdjArgs& A, const void* raw, const int64_t* raw_byte_off,
+                               const int32_t* orig_index, const GradPtrs* grads, hipStream_t st);
 }  // namespace csmap
 
 using namespace csmap;
@@ -647,6 +645,33 @@ csmap_status enqueue_render(csmap_sky* s, double* map, hipStream_t st, bool with
   }
   if (with_events) HIPCHK(s, hipEventRecord(s->ev[2], st), "event");
   return CSMAP_OK;
+}
+
+// Pixel chunks per group of 64 segments.  All items cost about the same, so
+// the launch ends in whole rounds of the wavefronts that fit the chip at once:
+// the fewest chunks that make at least two rounds and waste at most 4% of the
+// last one, else the least wasteful; chunks keep 128 pixels, about what an
+// item's set-up costs.
+int adjoint_chunks(int64_t groups, int64_t npix) {
+  int dev = 0, cus = 256;
+  (void)hipGetDevice(&dev);
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  const int64_t resident = 4 * (int64_t)cus * std::max(1, adjoint_blocks_per_cu());
+  const int64_t most = std::max<int64_t>(1, std::min<int64_t>(1024, npix / 128));
+  if (groups < 1) return 1;
+  int64_t best = most;
+  double least = 2.0;
+  for (int64_t n = 1; n <= most; ++n) {
+    const int64_t items = groups * n, rounds = (items + resident - 1) / resident;
+    if (items < 2 * resident && n < most) continue;
+    const double waste = 1.0 - (double)items / (double)(rounds * resident);
+    if (waste < least) {
+      least = waste;
+      best = n;
+    }
+    if (waste <= 0.04 || rounds >= 16) break;
+  }
+  return (int)best;
 }
 
 bool valid_pow_choice(int v) { return v == 1 || v == 2 || v == 4 || v == 8; }
@@ -1361,34 +1386,32 @@ csmap_status csmap_backward(csmap_sky* s, const double* dmap, const csmap_grad* 
   for (int64_t b = 0; b < nbox; ++b) groups += (kc[b].kept + 63) / 64;
   int nsplit = s->adj_split;
   if (nsplit <= 0) {
-    const int64_t target = 16384;  // work items wanted to fill the device
-    nsplit = (int)std::min<int64_t>(256, std::max<int64_t>(1, (target + std::max<int64_t>(groups, 1) - 1) /
-                                                                std::max<int64_t>(groups, 1)));
-    nsplit = (int)std::min<int64_t>(nsplit, std::max<int64_t>(1, s->npix / 64));
+    nsplit = adjoint_chunks(groups, s->npix);
   }
-  std::vector<int32_t> items;
-  items.reserve(3 * groups * nsplit);
-  for (int64_t b = 0; b < nbox; ++b)
-    for (int64_t g = 0; g < (kc[b].kept + 63) / 64; ++g)
-      for (int sp = 0; sp < nsplit; ++sp) {
-        items.push_back((int32_t)b);
-        items.push_back((int32_t)g);
-        items.push_back(sp);
-      }
-  const int64_t nitems = (int64_t)items.size() / 3;
+  // One upload: the groups of 64 records, and every box's gradient arrays.
+  if (groups > INT32_MAX) return fail(CSMAP_E_UNSUPPORTED, "too many segments for one backward");
+  const size_t ptr_bytes = sizeof(GradPtrs) * (size_t)std::max<int64_t>(nbox, 1);
+  std::vector<char> up(ptr_bytes + sizeof(AdjGroup) * (size_t)groups);
+  GradPtrs* const gp = (GradPtrs*)up.data();
+  AdjGroup* gr = (AdjGroup*)(up.data() + ptr_bytes);
+  for (int64_t b = 0; b < nbox; ++b) {
+    gp[b] = {grads[b].x_rel, grads[b].xdot, grads[b].xprime, grads[b].dsigma};
+    for (int64_t g = 0; g < (kc[b].kept + 63) / 64; ++g) *gr++ = {(int32_t)b, (int32_t)g};
+  }
   HIPCHK(s, s->d_pixtab32.ensure(sizeof(float) * 4 * (s->npix + 1)), "alloc pixel table");
   HIPCHK(s, s->d_pix64.ensure(sizeof(double) * 4 * s->npix), "alloc pixel table");
-  HIPCHK(s, s->d_partial.ensure(sizeof(double) * 14 * (size_t)std::max<int64_t>(1, s->total_seg) *
+  HIPCHK(s, s->d_partial.ensure(sizeof(double) * 14 * 64 * (size_t)std::max<int64_t>(1, groups) *
                                 nsplit), "alloc partials");
-  HIPCHK(s, s->d_adj_items.ensure(sizeof(int32_t) * std::max<size_t>(items.size(), 1)),
-         "alloc items");
-  if (!items.empty())
-    HIPCHK(s, hipMemcpyAsync(s->d_adj_items.p, items.data(), sizeof(int32_t) * items.size(),
-                             hipMemcpyHostToDevice, st), "upload items");
+  HIPCHK(s, s->d_adj_items.ensure(up.size()), "alloc items");
+  HIPCHK(s, hipMemcpyAsync(s->d_adj_items.p, up.data(), up.size(), hipMemcpyHostToDevice, st),
+         "upload items");
   HIPCHK(s, launch_pixtab(s->nside, s->npix, dmap, s->d_pixtab32.as<float>(),
                           s->d_pix64.as<double>(), st), "pixel table");
   for (int64_t b = 0; b < nbox; ++b) {
+    // Segments outside their slab get zero; where all are kept every element
+    // is written by the finalize step.
     const int64_t n = s->boxes[b].n;
+    if (kc[b].kept == n) continue;
     if (grads[b].x_rel) HIPCHK(s, launch_fill(grads[b].x_rel, 3 * n, 0.0, st), "grad clear");
     if (grads[b].xdot) HIPCHK(s, launch_fill(grads[b].xdot, 3 * n, 0.0, st), "grad clear");
     if (grads[b].xprime) HIPCHK(s, launch_fill(grads[b].xprime, 3 * n, 0.0, st), "grad clear");
@@ -1407,8 +1430,8 @@ csmap_status csmap_backward(csmap_sky* s, const double* dmap, const csmap_grad* 
   A.rec32 = s->d_rec32.as<float>();
   A.phat64 = s->d_phat64.as<double>();
   A.adjc = s->d_adjc.as<float>();
-  A.items = s->d_adj_items.as<int32_t>();
-  A.nitems = nitems;
+  A.groups = (const AdjGroup*)((const char*)s->d_adj_items.p + ptr_bytes);
+  A.ngroups = (int32_t)groups;
   A.nsplit = nsplit;
   A.near_w = (float)s->near_w;
   A.far_w = (float)std::max(s->far_w, s->near_w);
@@ -1417,15 +1440,8 @@ csmap_status csmap_backward(csmap_sky* s, const double* dmap, const csmap_grad* 
   HIPCHK(s, hipEventRecord(s->ev[4], st), "event");
   HIPCHK(s, launch_adjoint(A, st), "adjoint launch");
   HIPCHK(s, hipEventRecord(s->ev[5], st), "event");
-  for (int64_t b = 0; b < nbox; ++b) {
-    HIPCHK(s, launch_adj_finalize(s->d_boxes.as<DevBox>(), s->d_box_count.as<DevBoxCount>(),
-                                  (int32_t)b, kc[b].kept,
-                                  (const char*)s->raw.p + s->boxes[b].raw_byte_off,
-                                  s->d_orig.as<int32_t>(), s->d_phat64.as<double>(),
-                                  s->d_partial.as<double>(), nsplit, grads[b].x_rel,
-                                  grads[b].xdot, grads[b].xprime, grads[b].dsigma, st),
-           "finalize launch");
-  }
+  HIPCHK(s, launch_adj_finalize(A, s->raw.p, s->d_raw_off.as<int64_t>(), s->d_orig.as<int32_t>(),
+                                s->d_adj_items.as<GradPtrs>(), st), "finalize launch");
   // The item list lives in host memory until the copy has completed.
   HIPCHK(s, hipStreamSynchronize(st), "backward");
   s->have_bwd_time = true;

@@ -189,6 +189,16 @@ struct FwdArgs {
   unsigned long long* steps;     // FP32C: (wavefront, segment) steps of every form
 };
 
+// 64 consecutive kept records (one per lane) of a box, from record 64 group.
+struct AdjGroup {
+  int32_t box, group;
+};
+
+// The caller's gradient arrays of one box (any may be null).
+struct GradPtrs {
+  double *x, *xd, *xp, *ds;
+};
+
 // Arguments of the adjoint kernels.
 struct AdjArgs {
   const DevBox* boxes;
@@ -201,12 +211,12 @@ struct AdjArgs {
   const float* rec32;
   const double* phat64;
   const float* adjc;           // per record: constants per unit dsigma (see PreArgs)
-  const int32_t* items;        // (box, segment group, pixel chunk) triples
-  int64_t nitems;
-  int32_t nsplit;              // pixel chunks per segment group
+  const AdjGroup* groups;      // groups of 64 consecutive kept records of a box
+  int32_t ngroups;
+  int32_t nsplit;              // pixel chunks per group: item i is chunk i % nsplit of group i / nsplit
   float near_w;
   float far_w;
-  double* partial;             // [record][split][13] accumulators
+  double* partial;             // [split][accumulator][64 group + lane]
   const double* dmap;
 };
 

@@ -1793,7 +1793,10 @@ constexpr int kAcc = 14;
 // cotangent, a, b, w, v = Xdot.d, u = X'.d, r = 1/(b w), d = n - Ph.
 // With g = s r: S1 += g b, S2 += g a, SF += g m, C4 += g u,
 // C2 += (g u) a (w r), D3 += (g m)(b r) d, DV += (g b + C2 term) d,
-// DT += (g a + g u) d: 28 instructions.
+// DT += (g a + g u) d.  The z components of DV and DT are left out: over a
+// run of pixels with one d_z they are d_z (S1 + C2) and d_z (S2 + C4), added
+// when the run ends (a close pixel adds what its d_z differs by).
+// 25 instructions.
 __device__ __forceinline__ void adj_accumulate(float (&pa)[kAcc], float s, float a, float bb,
                                                float w, float v, float u, float r, float dx,
                                                float dy, float dz) {
@@ -1814,11 +1817,9 @@ __device__ __forceinline__ void adj_accumulate(float (&pa)[kAcc], float s, float
   const float dv = fmaf(g, bb, c2);             // s/w + s a u r/b
   pa[8] = fmaf(dv, dx, pa[8]);
   pa[9] = fmaf(dv, dy, pa[9]);
-  pa[10] = fmaf(dv, dz, pa[10]);
   const float c3 = fmaf(g, a, gu);              // s r (u + a)
   pa[11] = fmaf(c3, dx, pa[11]);
   pa[12] = fmaf(c3, dy, pa[12]);
-  pa[13] = fmaf(c3, dz, pa[13]);
 }
 
 // Per-lane constants of the adjoint's segment (see k_adj32).
@@ -1828,100 +1829,164 @@ struct AdjSeg {
   double hx, hy, hz;   // Ph in FP64
 };
 
-// The adjoint's pixel loop over [p0, p1): pixel records stream through
-// scalar registers one step ahead (the table holds one padding record past
-// the last pixel, so the read ahead needs no bound); the values are copied
-// to vector registers so that the per-pair FMAs read vector operands only
-// (twice the issue rate of scalar operands).  kVis: the box has a
-// visibility rule, tested per pixel.  kForce: the group takes the FP64 form
-// against every pixel.  Without it the close-pair path is marked unlikely,
-// so that the far path runs straight through with the loop's back edge as
-// its one taken branch (with the uniform flag tested in the loop, it took
-// four to five per pixel, and the launch was 4% slower).
+// Ring (1 .. 4N-1) of RING pixel p.
+__device__ __forceinline__ int64_t ring_of_pixel(int64_t N, int64_t npix, int64_t p) {
+  const int64_t ncap = 2 * N * (N - 1);
+  if (p >= ncap && p < npix - ncap) return N + (p - ncap) / (4 * N);
+  const bool south = p >= ncap;
+  const int64_t q = south ? npix - 1 - p : p;
+  // Cap ring i holds pixels 2 i (i - 1) .. 2 i (i + 1) - 1.
+  int64_t i = (int64_t)((1.0 + sqrt(1.0 + 2.0 * (double)q)) * 0.5);
+  while (2 * i * (i - 1) > q) --i;
+  while (2 * i * (i + 1) <= q) ++i;
+  return south ? 4 * N - i : i;
+}
+
+// The adjoint's pixel loop over [p0, p1).  The wavefront copies 64 pixel
+// records at a time into its own LDS slots, the next 64 requested meanwhile,
+// and every lane reads them back one by one as vector registers (one
+// broadcast read per pixel; streamed through scalar registers, each pixel
+// took three copies to vector registers, whose FMAs run at twice the rate).
+// The pixels of a ring share z, so that the z parts of w, a, b and d are
+// formed once per run of one ring, whose ends are known from the ring
+// numbers; whether every pair of a run is far is settled once for the run,
+// so that the far loop has no test and no branch per pixel.  kVis: the box
+// has a visibility rule, tested per pixel.  kForce: the group takes the FP64
+// form against every pixel.
+// The far loop takes 37 vector instructions per pixel, unrolled by four; the
+// loop that streamed pixels through scalar registers and tested each pair
+// took 44.  12,000 segments against Nside 256: 8.1 against 8.8 ms; 4,000
+// against Nside 1024: 41.9 against 44.3.  (One loop with the test kept but
+// the records in LDS was slower, 11.9 ms: the compiler copied the
+// accumulators where the paths met.)
 template <bool kVis, bool kForce>
 __device__ __forceinline__ void adj_pixels(const AdjArgs& A, const DevBox& bx, const AdjSeg& g,
-                                           int64_t p0, int64_t p1, double (&acc)[kAcc]) {
+                                           int64_t p0, int64_t p1, float4* lds, int lane,
+                                           double (&acc)[kAcc]) {
   const float near_w = A.near_w, far_w = A.far_w;
-  cf4p tab = (cf4p)A.pixtab;
+  const float4* tab = (const float4*)A.pixtab;
   cd2p tab64 = (cd2p)A.pix64;
-  // The pixels of a ring share z: the z parts of w, a, b and d are formed
-  // once per ring (whenever the z of the next pixel differs).
-  uint32_t zbits = 0x40000000u;   // the bits of 2.0f: no pixel has z = 2
-  float wz = 0.f, az = 0.f, bz = 0.f, dzr = 0.f;
   constexpr int J = 64;
-  v4f cur = tab[p0];
+  const int64_t N = A.nside;
+  const float th_far = acosf(fmaxf(-1.0f, 1.0f - far_w));
+  auto ring_len = [&](int64_t i) {
+    const int64_t k = i < 4 * N - i ? i : 4 * N - i;
+    return 4 * (k < N ? k : N);
+  };
+  int64_t ring = uniform_i64(ring_of_pixel(N, A.npix, p0));
+  int64_t ring_end;   // one past the ring's last pixel
+  {
+    const int64_t ncap = 2 * N * (N - 1), k = 4 * N - ring;
+    ring_end = ring < N ? 2 * ring * (ring + 1)
+                        : (ring <= 3 * N ? ncap + (ring - N + 1) * 4 * N : A.npix - 2 * k * (k - 1));
+  }
+  auto request = [&](int64_t p) { return tab[p + lane < A.npix ? p + lane : A.npix]; };
+  float4 nxt = request(p0);
   for (int64_t pc = p0; pc < p1; pc += J) {
-    const int64_t pe = (pc + J < p1) ? pc + J : p1;
-    float pa[kAcc];
+    lds[lane] = nxt;
+    __builtin_amdgcn_wave_barrier();
+    nxt = request(pc + J);
+    // 32-bit counts keep the loop tests on the scalar unit.
+    const int32_t rest = (int32_t)(p1 - pc), np = rest < J ? rest : J;
+    int32_t i = 0;
+    while (i < np) {
+      if (i == (int32_t)(ring_end - pc)) ring_end += ring_len(++ring);
+      const int32_t to = (int32_t)(ring_end - pc);
+      const int32_t end = __builtin_amdgcn_readfirstlane(to < np ? to : np);
+      const float z = lds[i].z;
+      const float wz = fmaf(-z, g.pz, 1.0f), az = z * g.tz, bz = fmaf(z, g.vz, 1.0f);
+      const float dzr = z - g.pz;
+      // Whether every pair of the run is far: its pixels lie within rho of
+      // its middle one (chord to the farther end; runs of more than half a
+      // ring, or of a chord past 1, are not asked).
+      bool far = false;
+      if (!kForce && 2 * (int64_t)(end - i) <= ring_len(ring)) {
+        const float4 c = lds[(i + end) >> 1], e0 = lds[i], e1 = lds[end - 1];
+        const float d0 = fmaf(c.x - e0.x, c.x - e0.x, (c.y - e0.y) * (c.y - e0.y));
+        const float d1 = fmaf(c.x - e1.x, c.x - e1.x, (c.y - e1.y) * (c.y - e1.y));
+        const float chord = sqrtf(fmaxf(d0, d1));
+        const float w = fmaf(-c.y, g.py, fmaf(-c.x, g.px, wz));
+        far = chord < 1.0f && !__any(w < versine(th_far + 1.05f * chord + 1e-6f));
+      }
+      float pa[kAcc];
 #pragma unroll
-    for (int k = 0; k < kAcc; ++k) pa[k] = 0.f;
-    // A 32-bit count keeps the loop test on the scalar unit (it has no
-    // 64-bit ordered compare).
-    const int32_t np = (int32_t)(pe - pc);   // at most J
-    for (int32_t i = 0; i < np; ++i) {
-      const int64_t p = pc + i;
-      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): cur has arrived
-      const v4f pt = cur;
-      cur = tab[p + 1];
-      if (kVis) {
-        const v2d e0 = tab64[2 * p + 0];
-        const v2d e1 = tab64[2 * p + 1];
-        if (!sees_box(e0.x, e0.y, e1.x, bx, A.eta0)) continue;
-      }
-      // A new ring (compared as bits, so that the test stays in scalar
-      // registers).
-      if (__float_as_uint(pt.z) != zbits) {
-        zbits = __float_as_uint(pt.z);
-        const float z = to_vgpr(pt.z);
-        wz = fmaf(-z, g.pz, 1.0f);
-        az = z * g.tz;
-        bz = fmaf(z, g.vz, 1.0f);
-        dzr = z - g.pz;
-      }
-      const float nx = to_vgpr(pt.x), ny = to_vgpr(pt.y);
-      float s = to_vgpr(pt.w);
-      float w = fmaf(-ny, g.py, fmaf(-nx, g.px, wz));
-      const float a = fmaf(ny, g.ty, fmaf(nx, g.tx, az));
-      const float bb = fmaf(ny, g.vy, fmaf(nx, g.vx, bz));
-      // The far form's values: Xdot.d = b - (1 + Ph.Xdot), X'.d = a - Ph.X'.
-      // A close pixel (for some lane) overwrites them in place, which lets
-      // the far form run without register copies.
-      float dx = nx - g.px, dy = ny - g.py, dz = dzr;
-      float v = bb - g.c1, u = a - g.c2;
-      if (kForce || __builtin_expect(__any(w < far_w), 0)) {
-        // Middle form: the direction difference in FP32 (see the forward
-        // kernel); FP64 form: from the FP64 directions.
-        if (kForce || __any(w < near_w)) {
-          const v2d e0 = tab64[2 * p + 0];
-          const v2d e1 = tab64[2 * p + 1];
-          dx = (float)(e0.x - g.hx);
-          dy = (float)(e0.y - g.hy);
-          dz = (float)(e1.x - g.hz);
+      for (int k = 0; k < kAcc; ++k) pa[k] = 0.f;
+      const int32_t from = __builtin_amdgcn_readfirstlane(i);
+      i = end;
+      if (far) {
+#pragma unroll 4
+        for (int32_t q = from; q < end; ++q) {
+          const float4 pt = lds[q];
+          if (kVis) {
+            const v2d e0 = tab64[2 * (pc + q)];
+            const v2d e1 = tab64[2 * (pc + q) + 1];
+            if (!sees_box(e0.x, e0.y, e1.x, bx, A.eta0)) continue;
+          }
+          const float w = fmaf(-pt.y, g.py, fmaf(-pt.x, g.px, wz));
+          const float a = fmaf(pt.y, g.ty, fmaf(pt.x, g.tx, az));
+          const float bb = fmaf(pt.y, g.vy, fmaf(pt.x, g.vx, bz));
+          // Xdot.d = b - (1 + Ph.Xdot), X'.d = a - Ph.X'.
+          adj_accumulate(pa, pt.w, a, bb, w, bb - g.c1, a - g.c2, __builtin_amdgcn_rcpf(bb * w),
+                         pt.x - g.px, pt.y - g.py, dzr);
         }
-        const float q = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-        v = fmaf(g.vz, dz, fmaf(g.vy, dy, g.vx * dx));
-        u = fmaf(g.tz, dz, fmaf(g.ty, dy, g.tx * dx));
-        // An exact coincidence (q = 0) contributes nothing.
-        w = (q > 0.0f) ? 0.5f * q : 1.0f;
-        s = (q > 0.0f) ? s : 0.0f;
+      } else {
+        for (int32_t j = from; j < end; ++j) {
+          const int64_t p = pc + j;
+          const float4 pt = lds[j];
+          if (kVis) {
+            const v2d e0 = tab64[2 * p + 0];
+            const v2d e1 = tab64[2 * p + 1];
+            if (!sees_box(e0.x, e0.y, e1.x, bx, A.eta0)) continue;
+          }
+          const float nx = pt.x, ny = pt.y;
+          float s = pt.w;
+          float w = fmaf(-ny, g.py, fmaf(-nx, g.px, wz));
+          const float a = fmaf(ny, g.ty, fmaf(nx, g.tx, az));
+          const float bb = fmaf(ny, g.vy, fmaf(nx, g.vx, bz));
+          float dx = nx - g.px, dy = ny - g.py, dz = dzr;
+          float v = bb - g.c1, u = a - g.c2;
+          if (kForce || __any(w < far_w)) {
+            // Middle form: the direction difference in FP32 (see the forward
+            // kernel); FP64 form: from the FP64 directions.
+            if (kForce || __any(w < near_w)) {
+              const v2d e0 = tab64[2 * p + 0];
+              const v2d e1 = tab64[2 * p + 1];
+              dx = (float)(e0.x - g.hx);
+              dy = (float)(e0.y - g.hy);
+              dz = (float)(e1.x - g.hz);
+            }
+            const float q = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+            v = fmaf(g.vz, dz, fmaf(g.vy, dy, g.vx * dx));
+            u = fmaf(g.tz, dz, fmaf(g.ty, dy, g.tx * dx));
+            // An exact coincidence (q = 0) contributes nothing.
+            w = (q > 0.0f) ? 0.5f * q : 1.0f;
+            s = (q > 0.0f) ? s : 0.0f;
+          }
+          const float r = __builtin_amdgcn_rcpf(bb * w), gr = s * r, gu = gr * u, dze = dz - dzr;
+          pa[10] = fmaf(fmaf(gr, bb, (gu * a) * (w * r)), dze, pa[10]);
+          pa[13] = fmaf(fmaf(gr, a, gu), dze, pa[13]);
+          adj_accumulate(pa, s, a, bb, w, v, u, r, dx, dy, dz);
+        }
       }
-      adj_accumulate(pa, s, a, bb, w, v, u, __builtin_amdgcn_rcpf(bb * w), dx, dy, dz);
-    }
+      pa[10] = fmaf(dzr, pa[0] + pa[3], pa[10]);
+      pa[13] = fmaf(dzr, pa[1] + pa[4], pa[13]);
 #pragma unroll
-    for (int k = 0; k < kAcc; ++k) acc[k] += (double)pa[k];
+      for (int k = 0; k < kAcc; ++k) acc[k] += (double)pa[k];
+    }
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
 // Work item: a group of 64 consecutive kept records of one box (one per
 // lane) and one of `nsplit` contiguous pixel ranges.
-__global__ void __launch_bounds__(256) k_adj32(AdjArgs A) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_adj32(AdjArgs A) {
   const int lane = threadIdx.x & 63;
   const int wpb = blockDim.x >> 6;
   const int64_t item = (int64_t)blockIdx.x * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (item >= A.nitems) return;
-  const int32_t b = ((ci32p)A.items)[3 * item + 0];
-  const int32_t grp = ((ci32p)A.items)[3 * item + 1];
-  const int32_t split = ((ci32p)A.items)[3 * item + 2];
+  if (item >= (int64_t)A.ngroups * A.nsplit) return;
+  const int32_t at = (int32_t)(item / A.nsplit), split = (int32_t)(item - (int64_t)at * A.nsplit);
+  const int32_t b = ((ci32p)A.groups)[2 * at + 0];
+  const int32_t grp = ((ci32p)A.groups)[2 * at + 1];
   const DevBox bx = load_box(A.boxes, b);
   const int64_t kept = load_kept(A.box_count, b);
   const int64_t li = (int64_t)grp * 64 + lane;
@@ -1944,33 +2009,28 @@ __global__ void __launch_bounds__(256) k_adj32(AdjArgs A) {
   // A group holding a segment flagged at precompute takes the FP64 form
   // against every pixel.
   const bool force = __any(active && __float_as_int(q3.y) != 0);
+  __shared__ float4 px[4][64];
+  float4* const lds = px[threadIdx.x >> 6];
   double acc[kAcc];
 #pragma unroll
   for (int k = 0; k < kAcc; ++k) acc[k] = 0.0;
   if (force) {
     if (bx.vis != 0)
-      adj_pixels<true, true>(A, bx, g, p0, p1, acc);
+      adj_pixels<true, true>(A, bx, g, p0, p1, lds, lane, acc);
     else
-      adj_pixels<false, true>(A, bx, g, p0, p1, acc);
+      adj_pixels<false, true>(A, bx, g, p0, p1, lds, lane, acc);
   } else {
     if (bx.vis != 0)
-      adj_pixels<true, false>(A, bx, g, p0, p1, acc);
+      adj_pixels<true, false>(A, bx, g, p0, p1, lds, lane, acc);
     else
-      adj_pixels<false, false>(A, bx, g, p0, p1, acc);
+      adj_pixels<false, false>(A, bx, g, p0, p1, lds, lane, acc);
   }
-  if (active) {
-    double* o = A.partial + ((size_t)rec * A.nsplit + split) * kAcc;
+  // Lanes past the box's last record repeat its first and are not read.
+  const int64_t slots = 64 * (int64_t)A.ngroups;
+  double* o = A.partial + (int64_t)split * kAcc * slots + 64 * (int64_t)at + lane;
 #pragma unroll
-    for (int k = 0; k < kAcc; ++k) o[k] = acc[k];
-  }
+  for (int k = 0; k < kAcc; ++k) o[k * slots] = acc[k];
 }
-
-struct GradPtrs {
-  double* x;
-  double* xd;
-  double* xp;
-  double* ds;
-};
 
 // Combine the pixel-chunk partials of each kept record (in chunk order) and
 // apply the per-segment chain rule, then scatter to the caller's arrays.
@@ -1981,22 +2041,53 @@ struct GradPtrs {
 //   dL/dV = dsigma [DV + Ph C2 + SF V/(1 - V^2)]        (the last term from eps)
 //   dL/dT = dsigma [-DT - Ph C4 + SF T/T^2]             (the last term from eps)
 //   dL/ddsigma = SF                            (Eq. (1) is linear in dsigma)
-__global__ void k_adj_finalize(const DevBox* boxes, const DevBoxCount* counts, int32_t b,
-                               const char* raw, const int32_t* orig_index,
-                               const double* phat64, const double* partial, int32_t nsplit,
-                               GradPtrs out) {
-  const DevBox bx = boxes[b];
-  const int64_t li = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (li >= counts[b].kept) return;
-  const int64_t rec = bx.rec_off + li;
+// One workgroup per group of 64 records, all boxes in one launch: its
+// wavefronts each add a run of the chunks in order (28 loads of 512 bytes in
+// flight), then the runs are added in order.  The loads' latency bounds it: a
+// thread per record reading its chunks one after another, a launch per box,
+// took 65-76 us per box (1,500 records, 86 chunks), eight such boxes 521-608;
+// one launch over the eight takes 19.
+constexpr int kFinWaves = 8;
+__global__ void __launch_bounds__(64 * kFinWaves) k_adj_finalize(AdjArgs A, const void* raw_base,
+                                                                 const int64_t* raw_byte_off,
+                                                                 const int32_t* orig_index,
+                                                                 const GradPtrs* grads) {
+  __shared__ double sum[kFinWaves][kAcc][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int32_t at = blockIdx.x;
+  const int64_t slots = 64 * (int64_t)A.ngroups;
   double S[kAcc];
 #pragma unroll
   for (int k = 0; k < kAcc; ++k) S[k] = 0.0;
-  for (int sp = 0; sp < nsplit; ++sp) {
-    const double* pp = partial + ((size_t)rec * nsplit + sp) * kAcc;
+  const int32_t s1 = A.nsplit * (wave + 1) / nw;
+  int32_t sp = A.nsplit * wave / nw;
+  const double* pp = A.partial + (int64_t)sp * kAcc * slots + 64 * (int64_t)at + lane;
+  for (; sp + 2 <= s1; sp += 2, pp += 2 * kAcc * slots) {
+    double t[2 * kAcc];
 #pragma unroll
-    for (int k = 0; k < kAcc; ++k) S[k] += pp[k];
+    for (int k = 0; k < 2 * kAcc; ++k) t[k] = pp[k * slots];
+#pragma unroll
+    for (int k = 0; k < kAcc; ++k) S[k] = (S[k] + t[k]) + t[kAcc + k];
   }
+  if (sp < s1)
+#pragma unroll
+    for (int k = 0; k < kAcc; ++k) S[k] += pp[k * slots];
+#pragma unroll
+  for (int k = 0; k < kAcc; ++k) sum[wave][k][lane] = S[k];
+  __syncthreads();
+  if (wave != 0) return;
+  for (int w = 1; w < nw; ++w)
+#pragma unroll
+    for (int k = 0; k < kAcc; ++k) S[k] += sum[w][k][lane];
+  const int32_t b = ((ci32p)A.groups)[2 * at];
+  const DevBox bx = load_box(A.boxes, b);
+  const int64_t li = 64 * (int64_t)((ci32p)A.groups)[2 * at + 1] + lane;
+  if (li >= load_kept(A.box_count, b)) return;
+  const int64_t rec = bx.rec_off + li;
+  const char* raw = (const char*)raw_base + raw_byte_off[b];
+  const double* phat64 = A.phat64;
+  const GradPtrs out = grads[b];
   const int64_t i = orig_index[rec];
   const int dt = bx.dtype;
   const int64_t n = bx.n;
@@ -2197,22 +2288,26 @@ hipError_t launch_pixtab(int64_t nside, int64_t npix, const double* dmap, float*
   return hipGetLastError();
 }
 
+// Workgroups (four wavefronts) of the adjoint pair kernel on one CU.
+int adjoint_blocks_per_cu() {
+  int nb = 0;
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_adj32, 256, 0);
+  return e == hipSuccess ? nb : 0;
+}
+
 hipError_t launch_adjoint(const AdjArgs& A, hipStream_t st) {
-  if (A.nitems == 0) return hipSuccess;
-  const unsigned grid = (unsigned)((A.nitems + 3) / 4);
+  if (A.ngroups == 0) return hipSuccess;
+  const unsigned grid = (unsigned)(((int64_t)A.ngroups * A.nsplit + 3) / 4);
   k_adj32<<<dim3(grid), dim3(256), 0, st>>>(A);
   return hipGetLastError();
 }
 
-hipError_t launch_adj_finalize(const DevBox* boxes, const DevBoxCount* counts, int32_t b,
-                               int64_t nseg, const char* raw, const int32_t* orig_index,
-                               const double* phat64, const double* partial, int32_t nsplit,
-                               double* gx, double* gxd, double* gxp, double* gds,
-                               hipStream_t st) {
-  if (nseg <= 0) return hipSuccess;
-  GradPtrs o{gx, gxd, gxp, gds};
-  k_adj_finalize<<<dim3((unsigned)((nseg + 255) / 256)), dim3(256), 0, st>>>(
-      boxes, counts, b, raw, orig_index, phat64, partial, nsplit, o);
+hipError_t launch_adj_finalize(const AdjArgs& A, const void* raw, const int64_t* raw_byte_off,
+                               const int32_t* orig_index, const GradPtrs* grads, hipStream_t st) {
+  if (A.ngroups == 0) return hipSuccess;
+  const int nw = A.nsplit < kFinWaves ? A.nsplit : kFinWaves;
+  k_adj_finalize<<<dim3((unsigned)A.ngroups), dim3(64 * nw), 0, st>>>(A, raw, raw_byte_off,
+                                                                     orig_index, grads);
   return hipGetLastError();
 }
 
