@@ -352,7 +352,8 @@ csmap_status csmap_render_flat(csmap_sky *sky, const csmap_patch *patch, double 
 csmap_status csmap_backward(csmap_sky *sky, const double *dmap, const csmap_grad *grads,
                             int64_t nbox);
 
-/* Drop all boxes (device memory is kept for reuse). */
+/* Drop all boxes (device memory is kept for reuse).  Work already enqueued
+ * goes on; boxes added next are copied behind it in stream order. */
 csmap_status csmap_reset(csmap_sky *sky);
 
 /* Free the sky and everything it owns.  NULL is accepted. */

@@ -344,6 +344,10 @@ class Sky:
             bid = csmap_add_cone_box(self.handle, b, cone, snapshot)
         else:
             bid = (csmap_add_snapshot_box if snapshot else csmap_add_box)(self.handle, b)
+        # The copy runs on the sky's stream after this returns (and after a
+        # reset): tell torch's allocator, which may know another stream.
+        for t in (x_rel, xdot, xprime, dsigma):
+            t.record_stream(self.stream)
         self._keep.append((x_rel, xdot, xprime, dsigma))
         self.box_shapes.append(n)
         self.box_dtypes.append(dt)

@@ -24,6 +24,8 @@
 
 namespace csmap {
 hipError_t launch_precompute(const PreArgs& A, int64_t nbox, hipStream_t st);
+hipError_t launch_copy_box(void* dst, const void* const src[4], int64_t n, size_t es,
+                           hipStream_t st);
 hipError_t launch_fill(double* p, int64_t n, double v, hipStream_t st);
 hipError_t launch_zero_counters(unsigned long long* c, int n, uint32_t* work, hipStream_t st);
 hipError_t launch_pix2vec(int64_t nside, int64_t first, int64_t count, double* xyz,
@@ -155,19 +157,31 @@ struct csmap_sky {
   Tiling plan;
   DevBuf d_rows;     // ring-block row table (empty for strips)
   DevBuf d_frames;   // tile frames (matrix-core forward)
-  DevBuf d_boxes, d_blk_box, d_blk_count, d_blk_prefix, d_box_count, d_raw_off, d_blk_mask;
+  DevBuf d_blk_count, d_blk_prefix, d_box_count, d_blk_mask;
+  // Descriptors and tile lists, one upload from h_plan; up_ev marks when the
+  // copy has read it.
+  DevBuf d_plan;
+  std::vector<char> h_plan;
+  hipEvent_t up_ev = nullptr;
+  bool up_pending = false;
+  DevBox* p_boxes = nullptr;
+  int64_t* p_raw_off = nullptr;
+  int32_t *p_blk_box = nullptr, *p_tile_ptr = nullptr, *p_tile_boxes = nullptr;
+  int32_t* p_box_items = nullptr;
+  WorkItem* p_work = nullptr;
   DevBuf d_flat_off, d_flat_rec, d_flat_part;
   DevBuf d_udir;      // caller directions of csmap_render_dirs, x | y | z
   DevBuf d_part;      // partial tiles of record slices (render; held by a captured graph)
   DevBuf d_udir_part; // csmap_render_dirs: the same
   DevBuf d_rec32, d_recm, d_phat64, d_rec64, d_orig;
-  DevBuf d_tile_ptr, d_tile_boxes, d_items, d_box_items;
-  std::vector<int64_t> box_items_off;  // per box offset into d_box_items (+ end)
+  std::vector<int64_t> box_items_off;  // per-box schedule: offsets into p_box_items (+ end)
+  bool box_lists = false;              // p_box_items holds the plan's tiles per box
   int64_t nblk = 0;
   int64_t ntiles = 0;
-  // Persistent schedule: work items, then the sliced tiles, in d_items, and
-  // the partial tiles they take in d_part.
+  // Persistent schedule: work items, then the sliced tiles, at p_work (null
+  // where every tile takes nsplit slices), and the partial tiles in d_part.
   int64_t nwork = 0, nsplit_tiles = 0, part_tiles = 0;
+  int32_t nsplit = 1;
   int32_t max_slices = 1;
   bool all_boxes = true;
   DevBuf d_counters;  // [0] pairs, [1] FP64 steps, [2] work counter (uint32), [3] middle steps,
@@ -294,97 +308,72 @@ double planned_records(const HostBox& h) {
 
 FwdArgs fwd_args(csmap_sky* s, double* map);
 
+// Device descriptor of a box whose records and precompute blocks start at
+// rec_off and blk_off.
+void fill_box(const HostBox& h, int64_t rec_off, int64_t blk_off, DevBox& d) {
+  memset(&d, 0, sizeof(d));
+  for (int k = 0; k < 3; ++k) {
+    d.origin[k] = h.geom.origin[k];
+    d.ext[k] = h.geom.ext[k];
+    d.cap_dir[k] = h.geom.cap_dir[k];
+  }
+  d.eta_lo = h.geom.eta_lo;
+  d.eta_hi = h.geom.eta_hi;
+  d.cap_cos = h.geom.cap_cos;
+  d.vis = h.geom.vis;
+  d.dtype = h.dtype;
+  d.snapshot = h.snapshot;
+  d.rotated = h.rotated;
+  d.cone_nside = (int32_t)h.cone_nside;
+  d.cone_pix = h.cone_pix;
+  for (int k = 0; k < 9; ++k) d.rot[k] = h.rot[k];
+  for (int k = 0; k < 3; ++k) d.cone_dir[k] = h.cone_dir[k];
+  d.cone_cos_out = h.cone_cos_out;
+  d.cone_cos_in = h.cone_cos_in;
+  for (int e = 0; e < 4; ++e) {
+    for (int k = 0; k < 3; ++k) d.cone_n[e][k] = h.cone_edge.n[e][k];
+    d.cone_hi[e] = h.cone_edge.hi[e];
+    d.cone_lo[e] = h.cone_edge.lo[e];
+  }
+  d.n = h.n;
+  d.raw_off = 0;
+  d.rec_off = rec_off;
+  d.blk_off = blk_off;
+}
+
+// A section of the plan's upload: count elements at a 256-byte offset.
+template <class T>
+struct Section {
+  size_t off = 0, count = 0;
+  void place(size_t n, size_t& end) {
+    off = (end + 255) & ~(size_t)255;
+    count = n;
+    end = off + sizeof(T) * n;
+  }
+  T* in(char* base) const { return (T*)(base + off); }
+};
+
 // Rebuild descriptors, compaction tables, record storage and the tile plan.
+// What depends on the tiling alone is kept; the rest goes up in one copy from
+// h_plan, which the next call waits for before it writes there again, so that
+// this call does not wait for the stream (a map of Nside 64 took about a
+// third of its time in separate uploads and waits).
 csmap_status prepare(csmap_sky* s) {
-  if (!s->dirty && s->planned_K == s->K && s->planned_tiling == s->tiling &&
-      s->planned_rings == block_rings(s) && s->planned_matrix == use_matrix(s))
+  const bool matrix = use_matrix(s);
+  const bool lists = s->schedule == 2;
+  const bool same_tiles = s->tiles_ready && s->planned_K == s->K &&
+                          s->planned_tiling == s->tiling && s->planned_rings == block_rings(s);
+  if (!s->dirty && same_tiles && s->planned_matrix == matrix && (!lists || s->box_lists))
     return CSMAP_OK;
   const int64_t nbox = (int64_t)s->boxes.size();
   hipStream_t st = s->stream;
-  // Box descriptors and precompute blocks.
-  std::vector<DevBox> db(nbox);
-  std::vector<int32_t> blk_box;
-  std::vector<int64_t> raw_off(nbox);
-  int64_t rec = 0;
-  for (int64_t b = 0; b < nbox; ++b) {
-    const HostBox& h = s->boxes[b];
-    DevBox& d = db[b];
-    memset(&d, 0, sizeof(d));
-    for (int k = 0; k < 3; ++k) {
-      d.origin[k] = h.geom.origin[k];
-      d.ext[k] = h.geom.ext[k];
-      d.cap_dir[k] = h.geom.cap_dir[k];
-    }
-    d.eta_lo = h.geom.eta_lo;
-    d.eta_hi = h.geom.eta_hi;
-    d.cap_cos = h.geom.cap_cos;
-    d.vis = h.geom.vis;
-    d.dtype = h.dtype;
-    d.snapshot = h.snapshot;
-    d.rotated = h.rotated;
-    d.cone_nside = (int32_t)h.cone_nside;
-    d.cone_pix = h.cone_pix;
-    for (int k = 0; k < 9; ++k) d.rot[k] = h.rot[k];
-    for (int k = 0; k < 3; ++k) d.cone_dir[k] = h.cone_dir[k];
-    d.cone_cos_out = h.cone_cos_out;
-    d.cone_cos_in = h.cone_cos_in;
-    for (int e = 0; e < 4; ++e) {
-      for (int k = 0; k < 3; ++k) d.cone_n[e][k] = h.cone_edge.n[e][k];
-      d.cone_hi[e] = h.cone_edge.hi[e];
-      d.cone_lo[e] = h.cone_edge.lo[e];
-    }
-    d.n = h.n;
-    d.raw_off = 0;
-    d.rec_off = rec;
-    d.blk_off = (int64_t)blk_box.size();
-    const int64_t nb = (h.n + kPreBlock - 1) / kPreBlock;
-    for (int64_t k = 0; k < nb; ++k) blk_box.push_back((int32_t)b);
-    raw_off[b] = h.raw_byte_off;
-    rec += h.n;
+  if (s->up_pending) {
+    HIPCHK(s, hipEventSynchronize(s->up_ev), "wait for the last plan's upload");
+    s->up_pending = false;
   }
-  s->nblk = (int64_t)blk_box.size();
-  const int64_t nrec = std::max<int64_t>(rec, 1);
-  HIPCHK(s, s->d_boxes.ensure(sizeof(DevBox) * std::max<int64_t>(nbox, 1)), "alloc boxes");
-  HIPCHK(s, s->d_blk_box.ensure(sizeof(int32_t) * std::max<int64_t>(s->nblk, 1)), "alloc blocks");
-  HIPCHK(s, s->d_blk_count.ensure(sizeof(int32_t) * std::max<int64_t>(s->nblk, 1)), "alloc blocks");
-  HIPCHK(s, s->d_blk_prefix.ensure(sizeof(int64_t) * std::max<int64_t>(s->nblk, 1)), "alloc blocks");
-  HIPCHK(s, s->d_blk_mask.ensure(sizeof(uint64_t) * kPreWords *
-                                 std::max<int64_t>(s->nblk, 1)), "alloc blocks");
-  HIPCHK(s, s->d_box_count.ensure(sizeof(DevBoxCount) * std::max<int64_t>(nbox, 1)), "alloc counts");
-  HIPCHK(s, s->d_raw_off.ensure(sizeof(int64_t) * std::max<int64_t>(nbox, 1)), "alloc offsets");
-  HIPCHK(s, s->d_orig.ensure(sizeof(int32_t) * nrec), "alloc records");
-  if (s->form == CSMAP_FORM_FP32C) {
-    HIPCHK(s, s->d_rec32.ensure(sizeof(float) * kRec32 * nrec), "alloc records");
-    if (use_matrix(s))
-      HIPCHK(s, s->d_recm.ensure(sizeof(float) * kRecM * nrec), "alloc records");
-    HIPCHK(s, s->d_phat64.ensure(sizeof(double) * 4 * nrec), "alloc records");
-  } else {
-    HIPCHK(s, s->d_rec64.ensure(sizeof(double) * kRec64 * nrec), "alloc records");
-    HIPCHK(s, s->d_phat64.ensure(sizeof(double) * 4 * nrec), "alloc records");
-  }
-  HIPCHK(s, s->d_counters.ensure(64), "alloc counters");
-  if (!s->dir_ready) {
-    HIPCHK(s, s->d_dir.ensure(sizeof(double) * 3 * (size_t)s->npix), "alloc direction table");
-    double* d = s->d_dir.as<double>();
-    HIPCHK(s, launch_dir_table(s->nside, s->npix, d, d + s->npix, d + 2 * s->npix, st),
-           "direction table");
-    s->dir_ready = true;
-  }
-  if (nbox) {
-    HIPCHK(s, hipMemcpyAsync(s->d_boxes.p, db.data(), sizeof(DevBox) * nbox,
-                             hipMemcpyHostToDevice, st), "upload boxes");
-    HIPCHK(s, hipMemcpyAsync(s->d_raw_off.p, raw_off.data(), sizeof(int64_t) * nbox,
-                             hipMemcpyHostToDevice, st), "upload offsets");
-  }
-  if (s->nblk)
-    HIPCHK(s, hipMemcpyAsync(s->d_blk_box.p, blk_box.data(), sizeof(int32_t) * s->nblk,
-                             hipMemcpyHostToDevice, st), "upload blocks");
-
-  // Tile plan.  The tiles, their rows and frames follow from the tiling alone
-  // and are kept while it stays, whatever the boxes.
+  // Tiles, their rows and frames.
   std::vector<int64_t> rows;
-  if (!s->tiles_ready || s->planned_K != s->K || s->planned_tiling != s->tiling ||
-      s->planned_rings != block_rings(s)) {
+  if (!same_tiles) {
     s->tiles_ready = s->frames_ready = false;
     if (use_blocks(s)) {
       const int G = block_rings(s);
@@ -399,107 +388,190 @@ csmap_status prepare(csmap_sky* s) {
     }
   }
   s->ntiles = s->plan.ntiles;
-  s->all_boxes = true;
-  for (auto& h : s->boxes)
-    if (h.geom.vis != 0) s->all_boxes = false;
-  std::vector<std::vector<std::pair<int64_t, int64_t>>> ranges(nbox);
-  std::vector<int64_t> cnt(s->ntiles + 1, 0);
-  std::vector<double> cost(s->ntiles, 0.0);
-  for (int64_t b = 0; b < nbox; ++b) {
-    box_tiles(s->plan, s->boxes[b].geom, s->eta0, ranges[b]);
-    for (auto& r : ranges[b])
-      for (int64_t t = r.first; t <= r.second; ++t) {
-        cnt[t + 1] += 1;
-        cost[t] += planned_records(s->boxes[b]);
+  s->all_boxes = !has_rules(s);
+  // Precompute blocks and records.
+  int64_t rec = 0;
+  s->nblk = 0;
+  for (const HostBox& h : s->boxes) {
+    s->nblk += (h.n + kPreBlock - 1) / kPreBlock;
+    rec += h.n;
+  }
+  const int64_t nrec = std::max<int64_t>(rec, 1);
+  HIPCHK(s, s->d_blk_count.ensure(sizeof(int32_t) * std::max<int64_t>(s->nblk, 1)), "alloc blocks");
+  HIPCHK(s, s->d_blk_prefix.ensure(sizeof(int64_t) * std::max<int64_t>(s->nblk, 1)), "alloc blocks");
+  HIPCHK(s, s->d_blk_mask.ensure(sizeof(uint64_t) * kPreWords *
+                                 std::max<int64_t>(s->nblk, 1)), "alloc blocks");
+  HIPCHK(s, s->d_box_count.ensure(sizeof(DevBoxCount) * std::max<int64_t>(nbox, 1)), "alloc counts");
+  HIPCHK(s, s->d_orig.ensure(sizeof(int32_t) * nrec), "alloc records");
+  if (s->form == CSMAP_FORM_FP32C) {
+    HIPCHK(s, s->d_rec32.ensure(sizeof(float) * kRec32 * nrec), "alloc records");
+    if (matrix) HIPCHK(s, s->d_recm.ensure(sizeof(float) * kRecM * nrec), "alloc records");
+  } else {
+    HIPCHK(s, s->d_rec64.ensure(sizeof(double) * kRec64 * nrec), "alloc records");
+  }
+  HIPCHK(s, s->d_phat64.ensure(sizeof(double) * 4 * nrec), "alloc records");
+  HIPCHK(s, s->d_counters.ensure(64), "alloc counters");
+  if (!s->dir_ready) {
+    HIPCHK(s, s->d_dir.ensure(sizeof(double) * 3 * (size_t)s->npix), "alloc direction table");
+    double* d = s->d_dir.as<double>();
+    HIPCHK(s, launch_dir_table(s->nside, s->npix, d, d + s->npix, d + 2 * s->npix, st),
+           "direction table");
+    s->dir_ready = true;
+  }
+  // Tiles of every box, where some do not see the whole sky or the schedule
+  // goes box by box; the boxes and the records of every tile.
+  std::vector<std::vector<std::pair<int64_t, int64_t>>> ranges;
+  std::vector<int32_t> tile_ptr;
+  std::vector<double> cost;
+  if (!s->all_boxes || lists) {
+    ranges.resize(nbox);
+    tile_ptr.assign(s->ntiles + 1, 0);
+    cost.assign(s->ntiles + 1, 0.0);
+    for (int64_t b = 0; b < nbox; ++b) {
+      box_tiles(s->plan, s->boxes[b].geom, s->eta0, ranges[b]);
+      const double n = planned_records(s->boxes[b]);
+      for (auto& r : ranges[b]) {   // differences, summed below
+        tile_ptr[r.first] += 1;
+        cost[r.first] += n;
+        if (r.second + 1 <= s->ntiles) {
+          tile_ptr[r.second + 1] -= 1;
+          cost[r.second + 1] -= n;
+        }
       }
+    }
+    int32_t in = 0, at = 0;
+    double c = 0.0;
+    for (int64_t t = 0; t < s->ntiles; ++t) {
+      in += tile_ptr[t];
+      c += cost[t];
+      cost[t] = in ? std::max(c, 0.0) : 0.0;
+      tile_ptr[t] = at;
+      at += in;
+    }
+    tile_ptr[s->ntiles] = at;
+    cost.resize(s->ntiles);
   }
-  std::vector<int32_t> tile_ptr(s->ntiles + 1, 0), tile_boxes;
-  if (!s->all_boxes) {
-    for (int64_t t = 0; t < s->ntiles; ++t) tile_ptr[t + 1] = (int32_t)(tile_ptr[t] + cnt[t + 1]);
-    tile_boxes.resize(std::max<int64_t>(tile_ptr[s->ntiles], 1));
-    std::vector<int32_t> fillp(tile_ptr.begin(), tile_ptr.end() - 1);
-    for (int64_t b = 0; b < nbox; ++b)
-      for (auto& r : ranges[b])
-        for (int64_t t = r.first; t <= r.second; ++t) tile_boxes[fillp[t]++] = (int32_t)b;
-    HIPCHK(s, s->d_tile_ptr.ensure(sizeof(int32_t) * tile_ptr.size()), "alloc tiles");
-    HIPCHK(s, s->d_tile_boxes.ensure(sizeof(int32_t) * tile_boxes.size()), "alloc tiles");
-    HIPCHK(s, hipMemcpyAsync(s->d_tile_ptr.p, tile_ptr.data(), sizeof(int32_t) * tile_ptr.size(),
-                             hipMemcpyHostToDevice, st), "upload tiles");
-    HIPCHK(s, hipMemcpyAsync(s->d_tile_boxes.p, tile_boxes.data(),
-                             sizeof(int32_t) * tile_boxes.size(), hipMemcpyHostToDevice, st),
-           "upload tiles");
-  }
-  // Persistent schedule: tiles in slices of about equal work, those of the
-  // costliest tiles first, and the list of sliced tiles behind them.
-  double total = 0.0;
-  for (double c : cost) total += c;
-  std::vector<int32_t> order(s->ntiles);
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(),
-                   [&](int32_t a, int32_t b) { return cost[a] > cost[b]; });
-  // A matrix-core item takes four wavefronts; tiles of skies with rules differ
-  // in cost per record too, so those get twice the items to level out.
-  const bool matrix = use_matrix(s);
+  // Work items (see slices_of).  A matrix-core item takes four wavefronts;
+  // tiles of skies with rules differ in cost per record too, so those get
+  // twice the items to level out.
   const double items = !matrix ? kSliceItems : (s->all_boxes ? kSliceItems / 4 : kSliceItems / 2);
   std::vector<WorkItem> work, split;
-  work.reserve(s->ntiles);
-  int32_t slot = 0;
-  s->max_slices = 1;
-  for (int32_t t : order) {
-    const int32_t ns = slices_of(cost[t], total, items, matrix);
-    s->max_slices = std::max(s->max_slices, ns);
-    for (int32_t k = 0; k < ns; ++k) work.push_back({t, k, ns, slot});
-    if (ns == 1) continue;
-    split.push_back({t, 0, ns, slot});
-    slot += ns;
+  s->nsplit = s->max_slices = 1;
+  if (s->all_boxes) {
+    double records = 0.0;
+    for (const HostBox& h : s->boxes) records += planned_records(h);
+    s->nsplit = s->max_slices = slices_of(records, records * (double)s->ntiles, items, matrix);
+    s->nwork = s->ntiles * s->nsplit;
+    s->part_tiles = s->nsplit > 1 ? s->nwork : 0;
+  } else {
+    // Tiles in slices of about equal work, those of the costliest tiles
+    // first, and the list of sliced tiles behind them.
+    double total = 0.0;
+    for (double c : cost) total += c;
+    std::vector<int32_t> order;
+    order_by_cost(cost, order);
+    work.reserve(s->ntiles);
+    int32_t slot = 0;
+    for (int32_t t : order) {
+      const int32_t ns = slices_of(cost[t], total, items, matrix);
+      s->max_slices = std::max(s->max_slices, ns);
+      for (int32_t k = 0; k < ns; ++k) work.push_back({t, k, ns, slot});
+      if (ns == 1) continue;
+      split.push_back({t, 0, ns, slot});
+      slot += ns;
+    }
+    s->nwork = (int64_t)work.size();
+    s->part_tiles = slot;
+    work.insert(work.end(), split.begin(), split.end());
   }
-  s->nwork = (int64_t)work.size();
   s->nsplit_tiles = (int64_t)split.size();
-  s->part_tiles = slot;
-  work.insert(work.end(), split.begin(), split.end());
-  HIPCHK(s, s->d_part.ensure(sizeof(double) * (size_t)tile_pixels(s) * (size_t)slot),
+  HIPCHK(s, s->d_part.ensure(sizeof(double) * (size_t)tile_pixels(s) * (size_t)s->part_tiles),
          "alloc partial tiles");
-  HIPCHK(s, s->d_items.ensure(sizeof(WorkItem) * work.size()), "alloc items");
-  HIPCHK(s, hipMemcpyAsync(s->d_items.p, work.data(), sizeof(WorkItem) * work.size(),
-                           hipMemcpyHostToDevice, st), "upload items");
-  // Per-box schedule: the tiles of each box.
-  std::vector<int32_t> bitems;
+  // The upload.
   s->box_items_off.assign(nbox + 1, 0);
+  if (lists)
+    for (int64_t b = 0; b < nbox; ++b) {
+      int64_t n = 0;
+      for (auto& r : ranges[b]) n += r.second - r.first + 1;
+      s->box_items_off[b + 1] = s->box_items_off[b] + n;
+    }
+  Section<DevBox> x_box;
+  Section<int64_t> x_raw;
+  Section<int32_t> x_blk, x_ptr, x_list, x_per_box;
+  Section<WorkItem> x_work;
+  size_t bytes = 0;
+  x_box.place((size_t)nbox, bytes);
+  x_raw.place((size_t)nbox, bytes);
+  x_blk.place((size_t)s->nblk, bytes);
+  x_work.place(work.size(), bytes);
+  x_ptr.place(s->all_boxes ? 0 : tile_ptr.size(), bytes);
+  x_list.place(s->all_boxes ? 0 : (size_t)tile_ptr[s->ntiles], bytes);
+  x_per_box.place((size_t)s->box_items_off[nbox], bytes);
+  s->h_plan.resize(std::max<size_t>(bytes, 256));
+  char* const h = s->h_plan.data();
+  HIPCHK(s, s->d_plan.ensure(s->h_plan.size()), "alloc plan");
+  DevBox* db = x_box.in(h);
+  int32_t* blk = x_blk.in(h);
+  int64_t at_rec = 0, at_blk = 0;
   for (int64_t b = 0; b < nbox; ++b) {
-    for (auto& r : ranges[b])
-      for (int64_t t = r.first; t <= r.second; ++t) bitems.push_back((int32_t)t);
-    s->box_items_off[b + 1] = (int64_t)bitems.size();
+    fill_box(s->boxes[b], at_rec, at_blk, db[b]);
+    x_raw.in(h)[b] = s->boxes[b].raw_byte_off;
+    const int64_t nb = (s->boxes[b].n + kPreBlock - 1) / kPreBlock;
+    for (int64_t k = 0; k < nb; ++k) blk[at_blk++] = (int32_t)b;
+    at_rec += s->boxes[b].n;
   }
-  HIPCHK(s, s->d_box_items.ensure(sizeof(int32_t) * std::max<size_t>(bitems.size(), 1)),
-         "alloc items");
-  if (!bitems.empty())
-    HIPCHK(s, hipMemcpyAsync(s->d_box_items.p, bitems.data(), sizeof(int32_t) * bitems.size(),
-                             hipMemcpyHostToDevice, st), "upload items");
-  if (use_matrix(s) && !s->frames_ready) {
+  if (!work.empty()) memcpy(x_work.in(h), work.data(), sizeof(WorkItem) * work.size());
+  if (!s->all_boxes) {
+    memcpy(x_ptr.in(h), tile_ptr.data(), sizeof(int32_t) * tile_ptr.size());
+    int32_t* list = x_list.in(h);
+    for (int64_t b = 0; b < nbox; ++b)   // boxes in order within each tile
+      for (auto& r : ranges[b])
+        for (int64_t t = r.first; t <= r.second; ++t) list[tile_ptr[t]++] = (int32_t)b;
+  }
+  if (lists)
+    for (int64_t b = 0; b < nbox; ++b) {
+      int32_t* o = x_per_box.in(h) + s->box_items_off[b];
+      for (auto& r : ranges[b])
+        for (int64_t t = r.first; t <= r.second; ++t) *o++ = (int32_t)t;
+    }
+  HIPCHK(s, hipMemcpyAsync(s->d_plan.p, h, s->h_plan.size(), hipMemcpyHostToDevice, st),
+         "upload plan");
+  HIPCHK(s, hipEventRecord(s->up_ev, st), "event");
+  s->up_pending = true;
+  char* const d = (char*)s->d_plan.p;
+  s->p_boxes = x_box.in(d);
+  s->p_raw_off = x_raw.in(d);
+  s->p_blk_box = x_blk.in(d);
+  s->p_work = work.empty() ? nullptr : x_work.in(d);
+  s->p_tile_ptr = x_ptr.in(d);
+  s->p_tile_boxes = x_list.in(d);
+  s->p_box_items = x_per_box.in(d);
+  if (matrix && !s->frames_ready) {
     HIPCHK(s, s->d_frames.ensure(sizeof(TileFrame) * (size_t)s->ntiles), "alloc tile frames");
     HIPCHK(s, launch_tile_frames(fwd_args(s, nullptr), s->ntiles, s->d_frames.as<TileFrame>(), st),
            "tile frames");
     s->frames_ready = true;
   }
-  // Host staging vectors go out of scope below: wait for the copies.
-  HIPCHK(s, hipStreamSynchronize(st), "upload plan");
+  // New rows come from this call's own memory: wait for that copy.
+  if (!rows.empty()) HIPCHK(s, hipStreamSynchronize(st), "upload rows");
   s->dirty = false;
   s->planned_K = s->K;
   s->planned_tiling = s->tiling;
   s->planned_rings = block_rings(s);
-  s->planned_matrix = use_matrix(s);
+  s->planned_matrix = matrix;
   s->tiles_ready = true;
+  s->box_lists = lists;
   return CSMAP_OK;
 }
 
 PreArgs pre_args(csmap_sky* s) {
   PreArgs A;
   memset(&A, 0, sizeof(A));
-  A.boxes = s->d_boxes.as<DevBox>();
-  A.blk_box = s->d_blk_box.as<int32_t>();
+  A.boxes = s->p_boxes;
+  A.blk_box = s->p_blk_box;
   A.nblk = s->nblk;
   A.raw = s->raw.p;
-  A.raw_byte_off = s->d_raw_off.as<int64_t>();
+  A.raw_byte_off = s->p_raw_off;
   A.eta0 = s->eta0;
   A.blk_count = s->d_blk_count.as<int32_t>();
   A.blk_prefix = s->d_blk_prefix.as<int64_t>();
@@ -519,12 +591,12 @@ PreArgs pre_args(csmap_sky* s) {
 FwdArgs fwd_args(csmap_sky* s, double* map) {
   FwdArgs A;
   memset(&A, 0, sizeof(A));
-  A.boxes = s->d_boxes.as<DevBox>();
+  A.boxes = s->p_boxes;
   A.box_count = s->d_box_count.as<DevBoxCount>();
   A.nbox = (int32_t)s->boxes.size();
   A.all_boxes = s->all_boxes ? 1 : 0;
-  A.tile_ptr = s->d_tile_ptr.as<int32_t>();
-  A.tile_boxes = s->d_tile_boxes.as<int32_t>();
+  A.tile_ptr = s->p_tile_ptr;
+  A.tile_boxes = s->p_tile_boxes;
   A.rows = s->plan.blocks ? s->d_rows.as<int64_t>() : nullptr;
   A.ring_g = s->plan.blocks ? s->plan.rings : 1;
   A.ring_shift = 0;   // log2(64 / ring_g): lane l serves ring l >> ring_shift of its tile
@@ -576,10 +648,12 @@ csmap_status check_forward(const csmap_sky* s, const FwdArgs& A, int K) {
   if (use_matrix(s) && (!s->planned_matrix ||
                         s->d_frames.cap < sizeof(TileFrame) * (size_t)t.ntiles))
     return fail(CSMAP_E_STATE, "tile frames do not match the tile plan");
-  if (!A.items && !A.work && A.nitems > t.ntiles)
+  if (!A.items && !A.work && A.nitems > t.ntiles * A.nsplit)
     return fail(CSMAP_E_STATE, "more work items than tiles");
-  if (A.work && (A.nitems != s->nwork || A.nsplit_tiles != s->nsplit_tiles ||
-                 s->d_part.cap < sizeof(double) * 64 * (size_t)K * (size_t)s->part_tiles))
+  if ((A.work || A.nsplit > 1) &&
+      (A.nitems != s->nwork || A.nsplit != s->nsplit || A.nsplit_tiles != s->nsplit_tiles ||
+       A.nitems > INT32_MAX ||
+       s->d_part.cap < sizeof(double) * 64 * (size_t)K * (size_t)s->part_tiles))
     return fail(CSMAP_E_STATE, "record slices do not match the launch");
   return CSMAP_OK;
 }
@@ -612,8 +686,9 @@ csmap_status enqueue_render(csmap_sky* s, double* map, hipStream_t st, bool with
   const PreArgs P = pre_args(s);
   FwdArgs A = fwd_args(s, map);
   if (s->schedule == 1) {
-    A.work = s->d_items.as<WorkItem>();
+    A.work = s->p_work;
     A.nitems = s->nwork;
+    A.nsplit = s->nsplit;
     A.split = s->nsplit_tiles ? A.work + s->nwork : nullptr;
     A.nsplit_tiles = s->nsplit_tiles;
     A.part = s->d_part.as<double>();
@@ -634,7 +709,7 @@ csmap_status enqueue_render(csmap_sky* s, double* map, hipStream_t st, bool with
       const int64_t n = s->box_items_off[b + 1] - s->box_items_off[b];
       if (n == 0 || s->boxes[b].n == 0) continue;
       A.only_box = (int32_t)b;
-      A.items = s->d_box_items.as<int32_t>() + s->box_items_off[b];
+      A.items = s->p_box_items + s->box_items_off[b];
       A.nitems = n;
       HIPCHK(s, sky_forward(s, false, A, st), "forward launch");
     }
@@ -717,7 +792,8 @@ csmap_status csmap_create_sky(int64_t nside, double eta0, csmap_form form, void*
       return dev_fail(nullptr, r, "event create");
     }
   }
-  hipError_t r = hipStreamCreateWithFlags(&s->cap_stream, hipStreamNonBlocking);
+  hipError_t r = hipEventCreateWithFlags(&s->up_ev, hipEventDisableTiming);
+  if (r == hipSuccess) r = hipStreamCreateWithFlags(&s->cap_stream, hipStreamNonBlocking);
   if (r != hipSuccess) {
     csmap_destroy_sky(s);
     return dev_fail(nullptr, r, "stream create");
@@ -733,14 +809,14 @@ csmap_status csmap_destroy_sky(csmap_sky* s) {
   drop_graph(s);
   for (auto& e : s->ev)
     if (e) (void)hipEventDestroy(e);
+  if (s->up_ev) (void)hipEventDestroy(s->up_ev);
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
-  DevBuf* bufs[] = {&s->raw, &s->d_boxes, &s->d_blk_box, &s->d_blk_count, &s->d_blk_prefix,
-                    &s->d_blk_mask, &s->d_flat_off, &s->d_flat_rec, &s->d_udir, &s->d_flat_part,
-                    &s->d_part, &s->d_udir_part, &s->d_rows, &s->d_frames,
-                    &s->d_box_count, &s->d_raw_off, &s->d_rec32, &s->d_recm, &s->d_phat64, &s->d_rec64,
-                    &s->d_orig, &s->d_tile_ptr, &s->d_tile_boxes, &s->d_items,
-                    &s->d_box_items, &s->d_counters, &s->d_pixtab32, &s->d_pix64,
-                    &s->d_partial, &s->d_adj_items, &s->d_adjc, &s->d_dir};
+  DevBuf* bufs[] = {&s->raw, &s->d_blk_count, &s->d_blk_prefix, &s->d_box_count, &s->d_blk_mask,
+                    &s->d_plan, &s->d_flat_off, &s->d_flat_rec, &s->d_flat_part, &s->d_udir,
+                    &s->d_part, &s->d_udir_part, &s->d_rows, &s->d_frames, &s->d_rec32,
+                    &s->d_recm, &s->d_phat64, &s->d_rec64, &s->d_orig, &s->d_counters,
+                    &s->d_pixtab32, &s->d_pix64, &s->d_partial, &s->d_adj_items, &s->d_adjc,
+                    &s->d_dir};
   for (DevBuf* b : bufs) b->release();
   delete s;
   return CSMAP_OK;
@@ -764,6 +840,20 @@ static csmap_status check_cone(const csmap_cone* c) {
                      m[2] * (m[3] * m[7] - m[4] * m[6]);
   if (!(det > 0.0)) return fail(CSMAP_E_INVALID, "rot must be a proper rotation (det +1)");
   return CSMAP_OK;
+}
+
+static bool on_this_device(const void* const src[4]) {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  for (int k = 0; k < 4; ++k) {
+    hipPointerAttribute_t at;
+    if (((uintptr_t)src[k] & 3) || hipPointerGetAttributes(&at, src[k]) != hipSuccess) {
+      (void)hipGetLastError();   // an ordinary host pointer is no error here
+      return false;
+    }
+    if (at.type != hipMemoryTypeDevice || at.device != dev) return false;
+  }
+  return true;
 }
 
 static csmap_status add_box_impl(csmap_sky* s, const csmap_box* box, int snapshot,
@@ -826,12 +916,16 @@ static csmap_status add_box_impl(csmap_sky* s, const csmap_box* box, int snapsho
   char* dst = (char*)s->raw.p + s->raw_used;
   const size_t n3 = es * 3 * (size_t)box->n;
   if (box->n > 0) {
-    HIPCHK(s, hipMemcpyAsync(dst, box->x_rel, n3, hipMemcpyDefault, s->stream), "copy x_rel");
-    HIPCHK(s, hipMemcpyAsync(dst + n3, box->xdot, n3, hipMemcpyDefault, s->stream), "copy xdot");
-    HIPCHK(s, hipMemcpyAsync(dst + 2 * n3, box->xprime, n3, hipMemcpyDefault, s->stream),
-           "copy xprime");
-    HIPCHK(s, hipMemcpyAsync(dst + 3 * n3, box->dsigma, es * (size_t)box->n, hipMemcpyDefault,
-                             s->stream), "copy dsigma");
+    // One kernel where all four arrays are this device's memory, else copies
+    // of whatever kind of memory each is.
+    const void* src[4] = {box->x_rel, box->xdot, box->xprime, box->dsigma};
+    if (on_this_device(src)) {
+      HIPCHK(s, launch_copy_box(dst, src, box->n, es, s->stream), "copy segments");
+    } else {
+      for (int k = 0; k < 4; ++k)
+        HIPCHK(s, hipMemcpyAsync(dst + k * n3, src[k], k < 3 ? n3 : es * (size_t)box->n,
+                                 hipMemcpyDefault, s->stream), "copy segments");
+    }
   }
   HostBox h;
   h.snapshot = snapshot;
@@ -1090,7 +1184,9 @@ csmap_status csmap_reset(csmap_sky* s) {
   g_err.clear();
   csmap_status cs = check_sky(s);
   if (cs != CSMAP_OK) return cs;
-  HIPCHK(s, hipStreamSynchronize(s->stream), "reset");
+  // The next boxes are copied in stream order behind whatever still reads
+  // these; only a graph in flight has to be waited for before it goes.
+  if (s->graph_exec) HIPCHK(s, hipStreamSynchronize(s->stream), "reset");
   s->boxes.clear();
   s->raw_used = 0;
   s->total_seg = 0;
@@ -1251,13 +1347,13 @@ csmap_status csmap_render_flat(csmap_sky* s, const csmap_patch* patch, double* m
   pa.flat_cos = P.accept_cos;
   FlatArgs A;
   memset(&A, 0, sizeof(A));
-  A.boxes = s->d_boxes.as<DevBox>();
+  A.boxes = s->p_boxes;
   A.box_count = s->d_box_count.as<DevBoxCount>();
-  A.blk_box = s->d_blk_box.as<int32_t>();
+  A.blk_box = s->p_blk_box;
   A.nblk = s->nblk;
   A.nbox = nbox;
   A.raw = s->raw.p;
-  A.raw_byte_off = s->d_raw_off.as<int64_t>();
+  A.raw_byte_off = s->p_raw_off;
   A.orig_index = s->d_orig.as<int32_t>();
   A.eta0 = s->eta0;
   for (int k = 0; k < 3; ++k) {
@@ -1419,7 +1515,7 @@ csmap_status csmap_backward(csmap_sky* s, const double* dmap, const csmap_grad* 
   }
   AdjArgs A;
   memset(&A, 0, sizeof(A));
-  A.boxes = s->d_boxes.as<DevBox>();
+  A.boxes = s->p_boxes;
   A.box_count = s->d_box_count.as<DevBoxCount>();
   A.nbox = (int32_t)nbox;
   A.nside = s->nside;
@@ -1440,7 +1536,7 @@ csmap_status csmap_backward(csmap_sky* s, const double* dmap, const csmap_grad* 
   HIPCHK(s, hipEventRecord(s->ev[4], st), "event");
   HIPCHK(s, launch_adjoint(A, st), "adjoint launch");
   HIPCHK(s, hipEventRecord(s->ev[5], st), "event");
-  HIPCHK(s, launch_adj_finalize(A, s->raw.p, s->d_raw_off.as<int64_t>(), s->d_orig.as<int32_t>(),
+  HIPCHK(s, launch_adj_finalize(A, s->raw.p, s->p_raw_off, s->d_orig.as<int32_t>(),
                                 s->d_adj_items.as<GradPtrs>(), st), "finalize launch");
   // The item list lives in host memory until the copy has completed.
   HIPCHK(s, hipStreamSynchronize(st), "backward");

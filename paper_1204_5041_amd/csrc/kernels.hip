@@ -513,6 +513,27 @@ __global__ void k_fill_f64(double* p, int64_t n, double v) {
   for (int64_t k = i; k < n; k += stride) p[k] = v;
 }
 
+// A box's four arrays (word counts n[k]) into its storage, one after another.
+struct CopyBox {
+  const uint32_t* src[4];
+  uint32_t* dst;
+  int64_t end[4];   // running word counts
+};
+
+__global__ void __launch_bounds__(256) k_copy_box(CopyBox c) {
+  const int64_t first = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+  uint32_t v[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int64_t w = first + 256 * j;
+    const int k = w < c.end[0] ? 0 : (w < c.end[1] ? 1 : (w < c.end[2] ? 2 : 3));
+    if (w < c.end[3]) v[j] = c.src[k][k ? w - c.end[k - 1] : w];
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (first + 256 * j < c.end[3]) c.dst[first + 256 * j] = v[j];
+}
+
 __global__ void k_zero_counters(unsigned long long* c, int n, uint32_t* work) {
   if (threadIdx.x < (unsigned)n) c[threadIdx.x] = 0ull;
   if (threadIdx.x == 0 && work) *work = 0u;
@@ -2146,6 +2167,21 @@ hipError_t launch_precompute(const PreArgs& A, int64_t nbox, hipStream_t st) {
   if (A.nblk) k_pre_count<<<dim3((unsigned)A.nblk), dim3(kPreThreads), 0, st>>>(A);
   k_pre_scan<<<dim3((unsigned)nbox), dim3(256), 0, st>>>(A, nbox);
   if (A.nblk) k_pre_emit<<<dim3((unsigned)A.nblk), dim3(kPreThreads), 0, st>>>(A);
+  return hipGetLastError();
+}
+
+// Arrays of 3n, 3n, 3n and n elements of es bytes (device memory, aligned to
+// 4 bytes) to dst, back to back.
+hipError_t launch_copy_box(void* dst, const void* const src[4], int64_t n, size_t es,
+                           hipStream_t st) {
+  CopyBox c;
+  const int64_t words = n * (int64_t)(es / 4);
+  c.dst = (uint32_t*)dst;
+  for (int k = 0; k < 4; ++k) {
+    c.src[k] = (const uint32_t*)src[k];
+    c.end[k] = k < 3 ? 3 * words * (k + 1) : 10 * words;
+  }
+  k_copy_box<<<dim3((unsigned)((10 * words + 1023) / 1024)), dim3(256), 0, st>>>(c);
   return hipGetLastError();
 }
 

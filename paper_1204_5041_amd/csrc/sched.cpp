@@ -6,6 +6,7 @@
 // contain a visible pixel, so every quantity here carries a margin.
 #include <math.h>
 #include <stdint.h>
+#include <string.h>
 
 #include <algorithm>
 #include <utility>
@@ -63,6 +64,43 @@ int64_t chunk_of(int64_t j, int64_t len, int64_t maxlen, int64_t width) {
 
 }  // namespace
 
+static void ring_angles(Tiling& t) {
+  const int64_t nring = 4 * t.nside - 1;
+  t.theta.resize(nring);
+  t.sin_theta.resize(nring);
+  t.z.resize(nring);
+  for (int64_t i = 1; i <= nring; ++i) {
+    const double z = ring_info(t.nside, i).z;
+    const double th = acos(std::max(-1.0, std::min(1.0, z)));
+    t.z[i - 1] = z;
+    t.theta[i - 1] = th;
+    t.sin_theta[i - 1] = sin(th);
+  }
+}
+
+void order_by_cost(const std::vector<double>& cost, std::vector<int32_t>& order) {
+  // Radix sort on the bits of the cost in single precision (in order, for
+  // non-negative values), inverted for decreasing order: three stable passes.
+  const size_t n = cost.size();
+  std::vector<uint32_t> key(n);
+  for (size_t i = 0; i < n; ++i) {
+    const float f = (float)cost[i];
+    uint32_t u;
+    memcpy(&u, &f, sizeof(u));
+    key[i] = ~u;
+  }
+  std::vector<int32_t> a(n), b(n);
+  for (size_t i = 0; i < n; ++i) a[i] = (int32_t)i;
+  for (int shift = 0; shift < 33; shift += 11) {
+    size_t start[2049] = {};
+    for (size_t i = 0; i < n; ++i) ++start[((key[i] >> shift) & 2047) + 1];
+    for (int k = 0; k < 2048; ++k) start[k + 1] += start[k];
+    for (size_t i = 0; i < n; ++i) b[start[(key[a[i]] >> shift) & 2047]++] = a[i];
+    a.swap(b);
+  }
+  order.swap(a);
+}
+
 void make_strips(int64_t nside, int64_t tile_px, Tiling& t) {
   t = Tiling();
   t.nside = nside;
@@ -70,6 +108,7 @@ void make_strips(int64_t nside, int64_t tile_px, Tiling& t) {
   t.blocks = false;
   const int64_t npix = 12 * nside * nside;
   t.ntiles = (npix + tile_px - 1) / tile_px;
+  ring_angles(t);
 }
 
 void make_ring_blocks(int64_t nside, int rings, int64_t width, Tiling& t) {
@@ -90,6 +129,7 @@ void make_ring_blocks(int64_t nside, int rings, int64_t width, Tiling& t) {
     t.block_first[rb + 1] = t.block_first[rb] + (maxlen + width - 1) / width;
   }
   t.ntiles = t.block_first[nblock];
+  ring_angles(t);
 }
 
 std::pair<int64_t, int64_t> Tiling::ring_span(int64_t i, int64_t j0, int64_t j1) const {
@@ -146,16 +186,21 @@ void cap_tiles(const Tiling& t, double cx, double cy, double cz, double rho,
   const double phc = atan2(cy, cx);
   const double sc = sin(thc);
   std::vector<std::pair<int64_t, int64_t>> tl;
-  for (int64_t i = 1; i < 4 * nside; ++i) {
+  // Rings within rho of the centre's colatitude (theta grows with the ring).
+  const double cos_rho = cos(rho);
+  const int64_t i0 =
+      std::lower_bound(t.theta.begin(), t.theta.end(), thc - rho - 1e-12) - t.theta.begin();
+  for (int64_t i = i0 + 1; i < 4 * nside; ++i) {
+    const double th = t.theta[i - 1];
+    if (th - thc > rho) break;
+    if (thc - th > rho) continue;
     const RingInfo r = ring_info(nside, i);
-    const double th = acos(std::max(-1.0, std::min(1.0, r.z)));
-    if (fabs(th - thc) > rho) continue;
-    const double s = sin(th);
+    const double s = t.sin_theta[i - 1];
     double half;  // azimuth half-width of the cap on this ring
     if (thc <= rho || thc >= M_PI - rho || s * sc <= 1e-300) {
       half = M_PI;  // the cap reaches a pole, or the ring is at a pole
     } else {
-      const double cd = (cos(rho) - r.z * zc) / (s * sc);
+      const double cd = (cos_rho - r.z * zc) / (s * sc);
       if (cd <= -1.0) half = M_PI;
       else if (cd >= 1.0) half = 0.0;
       else half = acos(cd);

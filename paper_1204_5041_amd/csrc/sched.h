@@ -37,6 +37,8 @@ struct Tiling {
   int64_t ntiles = 0;
   std::vector<int64_t> block_first;   // ring blocks: first tile of each block (+ end)
   std::vector<int64_t> block_maxlen;  // ring blocks: longest ring of each block
+  // Colatitude of ring i, its sine and cosine, at [i - 1] (set by make_*).
+  std::vector<double> theta, sin_theta, z;
 
   // Inclusive range of tiles that hold offsets [j0, j1] of ring i (1-based).
   std::pair<int64_t, int64_t> ring_span(int64_t i, int64_t j0, int64_t j1) const;
@@ -54,6 +56,9 @@ void ring_block_rows(const Tiling& t, std::vector<int64_t>& rows);
 // inclusive ranges (conservative: never omits a tile).
 void cap_tiles(const Tiling& t, double cx, double cy, double cz, double rho,
                std::vector<std::pair<int64_t, int64_t>>& out);
+
+// Tile indices by decreasing cost (non-negative), equal costs in index order.
+void order_by_cost(const std::vector<double>& cost, std::vector<int32_t>& order);
 
 void box_tiles(const Tiling& t, const HostBoxGeom& g, double eta0,
                std::vector<std::pair<int64_t, int64_t>>& out);
