@@ -406,8 +406,8 @@ csmap_status csmap_autotune(csmap_sky *sky, const char *cache_path);
  * i = m (2 lmax + 1 - m) / 2 + l.  0 <= lmax <= 4 Nside.  Enqueued on
  * hip_stream, which must belong to the current device; does not
  * synchronise.  The work's device scratch (about 16 (4 Nside)(lmax + 1) +
- * 8 (ceil(Nside / 256) + 1)(lmax + 1)(lmax + 2) bytes: 1.7 GB at Nside
- * 2048, lmax 4096) is taken in stream order from a
+ * 8 (ceil(Nside / 256) + 1)(lmax + 1)(lmax + 2) bytes, and below 64 MiB up to
+ * 8 ceil(Nside / 32) of the latter: 1.7 GB at Nside 2048, lmax 4096) is taken in stream order from a
  * memory pool that the library creates per device on first use and released
  * to it when the work ends; the pool keeps the memory for later calls until
  * the process ends.  CSMAP_E_NOMEM when the scratch cannot be had; errors of

@@ -30,13 +30,17 @@ namespace csmap {
 namespace {
 
 constexpr int kLegScale = 600;   // values are v * 2^(600 e)
-// Ring pairs summed by one lane of the Legendre kernel.  The wavefront
-// reduction of each group of eight degrees is spread over more pairs as this
-// grows, at the cost of registers.  With the Fourier-factor reload kept out
-// of the loop's live registers, 8 pairs take 162 VGPRs (three wavefronts per
-// SIMD); at Nside 2048, lmax 4096 the kernel took 7.7 ms with 6 pairs and
-// 6.4-6.7 ms with 8 (7 pairs: 140 VGPRs, slower than 8).
-constexpr int kRingsPerLane = 8;
+// Ring pairs summed by one lane of the Legendre kernel (R = 1, 2, 4 or 8).
+// The wavefront reduction of each group of eight degrees is spread over more
+// pairs as this grows, at the cost of registers.  With the Fourier-factor
+// reload kept out of the loop's live registers, 8 pairs take 162 VGPRs (three
+// wavefronts per SIMD); at Nside 2048, lmax 4096 the kernel took 7.7 ms with 6
+// pairs and 6.4-6.7 ms with 8 (7 pairs: 140 VGPRs, slower than 8).  Where 8
+// leave fewer wavefronts than kLegWaves, fewer pairs per lane give more of
+// them (kernel times with 8 pairs and by this rule: Nside 128, lmax 300, 42.7
+// and 28.6 us; Nside 256, lmax 512, about 80 and 53 us).
+constexpr int kLegMaxRings = 8;
+constexpr int64_t kLegWaves = 3072;   // three per SIMD
 constexpr int kAnchor = 32;      // Fourier twiddles are recomputed exactly every 32 pixels
 
 typedef const double __attribute__((address_space(4)))* cdp;
@@ -390,14 +394,11 @@ __device__ void fft_table_block(int64_t L, double* tab, int64_t blk) {
 }
 
 template <int T>
-__global__ void __launch_bounds__(T) k_ring_fft(int64_t nside, int64_t mmax, const double* map,
-                                                const double* tab, const double* ftab,
-                                                double* F) {
-  extern __shared__ double sm[];   // quarter twiddle table, then H points
+__device__ void ring_fft(double* sm, int64_t nside, int64_t mmax, const double* map,
+                         const double* tab, const double* ftab, double* F, int64_t i) {
   double* tl = sm;
   double* zs = sm + 2 * kTwQ;      // H complex values at fft_slot<true> positions
   fft_load_twiddles(tl, ftab);
-  const int64_t i = nside + blockIdx.x;
   const Ring r = ring_of(nside, i);
   const int L = (int)r.len, H = L / 2;
   const int e = __builtin_ctz((unsigned)H);
@@ -431,6 +432,14 @@ __global__ void __launch_bounds__(T) k_ring_fft(int64_t nside, int64_t mmax, con
   }
 }
 
+template <int T>
+__global__ void __launch_bounds__(T) k_ring_fft(int64_t nside, int64_t mmax, const double* map,
+                                                const double* tab, const double* ftab,
+                                                double* F) {
+  extern __shared__ double sm[];   // quarter twiddle table, then H points
+  ring_fft<T>(sm, nside, mmax, map, tab, ftab, F, nside + blockIdx.x);
+}
+
 // Step 1 for ring pairs of any length, Nside <= 4096: the polar caps, and the
 // belt when Nside is not a power of two.  North ring q and south ring 4N - q
 // both have L = 4i pixels, i = min(q, N), at azimuths 2 pi (j + 1/2)/L, or
@@ -451,11 +460,9 @@ __global__ void __launch_bounds__(T) k_ring_fft(int64_t nside, int64_t mmax, con
 // of 4i values before the unpacking, which pairs k with L - k.  One
 // workgroup per ring pair: T threads take the four D_r one after another, or
 // with kQuad four groups of T threads take one each, each in its own P points
-// of LDS.  Transforms of few points wait on LDS and barriers, not on work, so
-// they run the four side by side (the 127 ring pairs of Nside 128: 17.0 us
+// of LDS, and keep E_r and Z there too.  Transforms of few points wait on LDS
+// and barriers, not on work, so they run the four side by side (the 127 ring pairs of Nside 128: 17.0 us
 // with four wavefronts, 27.4 us with 512 threads taking the four in turn).
-constexpr int kCapPer = 8;             // transform positions per thread
-constexpr int kCapKappa = kCapPer / 2; // D_r values per thread (i <= 4 T)
 constexpr int64_t kChirpBeltMin = 1024;   // Nside * (lmax / 64) from which the belt takes it
 
 __host__ __device__ __forceinline__ int64_t pow2_at_least(int64_t v) {
@@ -472,9 +479,11 @@ __device__ __forceinline__ void chirp(int64_t n, int64_t len, double& c, double&
   s = -sp;
 }
 
-template <int T, bool kQuad>
+template <int T, bool kQuad, int kPer = 8>
 __device__ void ring_chirp(double* sm, int64_t nside, int64_t mmax, const double* map,
                            const double* ftab, double* zslot, double* F, int64_t rn) {
+  // Transform positions, and D_r values (i <= P / 2 + 1/2), of one thread.
+  constexpr int kKappa = (kPer + 1) / 2;
   double* tl = sm;
   fft_load_twiddles(tl, ftab);
   const int t = kQuad ? threadIdx.x % T : threadIdx.x;
@@ -501,9 +510,9 @@ __device__ void ring_chirp(double* sm, int64_t nside, int64_t mmax, const double
   }
   __syncthreads();
   fft_dif<false, T>(xs, P, tl, t);
-  double Br[kCapPer], Bi[kCapPer];
+  double Br[kPer], Bi[kPer];
 #pragma unroll
-  for (int j = 0; j < kCapPer; ++j) {
+  for (int j = 0; j < kPer; ++j) {
     const int p = t + j * T;
     const cplx b = p < P ? fft_get<false>(xs, p) : cplx{0.0, 0.0};
     Br[j] = b.r;
@@ -514,9 +523,9 @@ __device__ void ring_chirp(double* sm, int64_t nside, int64_t mmax, const double
   // n = t + j * T < i, shared by the four quarter-length DFTs:
   // the inputs y_n w_n, the outputs w_kappa (...) and the twist powers
   // e^{-2 pi i r kappa/L} = (e^{-2 pi i kappa/L})^r.
-  double wc[kCapKappa], ws[kCapKappa], tc[kCapKappa], ts[kCapKappa];
+  double wc[kKappa], ws[kKappa], tc[kKappa], ts[kKappa];
 #pragma unroll
-  for (int j = 0; j < kCapKappa; ++j) {
+  for (int j = 0; j < kKappa; ++j) {
     const int64_t n = t + (int64_t)j * T;
     wc[j] = ws[j] = tc[j] = ts[j] = 0.0;
     if (n < i) {
@@ -530,16 +539,19 @@ __device__ void ring_chirp(double* sm, int64_t nside, int64_t mmax, const double
   // E_r(kappa) = e^{-2 pi i r kappa / L} D_r(kappa), staged in the ring's Z
   // slot at r i + kappa: the radix-4 step below reads back, from the same
   // thread, exactly the four positions kappa + s i that it then writes.
+  // Side by side the four D_r keep E_r, and then Z_{kappa + s i}, at kappa of
+  // their own LDS points (region r, then s).
   double* Z = zslot + (rn < N ? 4 * rn * (rn - 1) : 8 * N * (int64_t)blockIdx.x);
+  double* const zl = sm + 2 * kTwQ;
 #pragma unroll
   for (int rr = 0; rr < (kQuad ? 1 : 4); ++rr) {
     const int r = kQuad ? quad : rr;
 #pragma unroll
-    for (int j = 0; j < kCapPer; ++j) {
+    for (int j = 0; j < kPer; ++j) {
       const int p = t + j * T;
       if (p < P) {
         double ar = 0.0, ai = 0.0;
-        if (j < kCapKappa && p < i) {
+        if (j < kKappa && p < i) {
           const double yr = xn[4 * p + r], yi = pair ? xsth[4 * p + r] : 0.0;
           ar = fma(yr, wc[j], -(yi * ws[j]));
           ai = fma(yr, ws[j], yi * wc[j]);
@@ -550,7 +562,7 @@ __device__ void ring_chirp(double* sm, int64_t nside, int64_t mmax, const double
     __syncthreads();
     fft_dif<false, T>(xs, P, tl, t);
 #pragma unroll
-    for (int j = 0; j < kCapPer; ++j) {
+    for (int j = 0; j < kPer; ++j) {
       const int p = t + j * T;
       if (p < P) {
         const cplx a = fft_get<false>(xs, p);
@@ -560,7 +572,7 @@ __device__ void ring_chirp(double* sm, int64_t nside, int64_t mmax, const double
     __syncthreads();
     fft_dit_inv<false, T>(xs, P, tl, t);
 #pragma unroll
-    for (int j = 0; j < kCapKappa; ++j) {
+    for (int j = 0; j < kKappa; ++j) {
       const int64_t kap = t + (int64_t)j * T;
       if (kap < i) {
         const cplx c = fft_get<false>(xs, (int)kap);
@@ -573,8 +585,12 @@ __device__ void ring_chirp(double* sm, int64_t nside, int64_t mmax, const double
           di = fma(dr, ts[j], di * tc[j]);
           dr = er;
         }
-        Z[2 * (r * i + kap)] = dr;
-        Z[2 * (r * i + kap) + 1] = di;
+        if constexpr (kQuad) {
+          fft_put<false>(xs, (int)kap, {dr, di});
+        } else {
+          Z[2 * (r * i + kap)] = dr;
+          Z[2 * (r * i + kap) + 1] = di;
+        }
       }
     }
     __syncthreads();
@@ -586,21 +602,32 @@ __device__ void ring_chirp(double* sm, int64_t nside, int64_t mmax, const double
       double Er[4], Ei[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        Er[r] = Z[2 * (r * i + kap)];
-        Ei[r] = Z[2 * (r * i + kap) + 1];
+        if constexpr (kQuad) {
+          const cplx e = fft_get<false>(zl, r * P + (int)kap);
+          Er[r] = e.r;
+          Ei[r] = e.i;
+        } else {
+          Er[r] = Z[2 * (r * i + kap)];
+          Ei[r] = Z[2 * (r * i + kap) + 1];
+        }
       }
       const double s0r = Er[0] + Er[2], s0i = Ei[0] + Ei[2];
       const double d0r = Er[0] - Er[2], d0i = Ei[0] - Ei[2];
       const double s1r = Er[1] + Er[3], s1i = Ei[1] + Ei[3];
       const double d1r = Er[1] - Er[3], d1i = Ei[1] - Ei[3];
-      Z[2 * kap] = s0r + s1r;                 // s = 0
-      Z[2 * kap + 1] = s0i + s1i;
-      Z[2 * (kap + i)] = d0r + d1i;           // s = 1: E0 - i E1 - E2 + i E3
-      Z[2 * (kap + i) + 1] = d0i - d1r;
-      Z[2 * (kap + 2 * i)] = s0r - s1r;       // s = 2
-      Z[2 * (kap + 2 * i) + 1] = s0i - s1i;
-      Z[2 * (kap + 3 * i)] = d0r - d1i;       // s = 3: E0 + i E1 - E2 - i E3
-      Z[2 * (kap + 3 * i) + 1] = d0i + d1r;
+      const cplx out[4] = {{s0r + s1r, s0i + s1i},    // s = 0
+                           {d0r + d1i, d0i - d1r},    // s = 1: E0 - i E1 - E2 + i E3
+                           {s0r - s1r, s0i - s1i},    // s = 2
+                           {d0r - d1i, d0i + d1r}};   // s = 3: E0 + i E1 - E2 - i E3
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if constexpr (kQuad) {
+          fft_put<false>(zl, q * P + (int)kap, out[q]);
+        } else {
+          Z[2 * (kap + q * i)] = out[q].r;
+          Z[2 * (kap + q * i) + 1] = out[q].i;
+        }
+      }
     }
   }
   __syncthreads();
@@ -609,7 +636,16 @@ __device__ void ring_chirp(double* sm, int64_t nside, int64_t mmax, const double
   const int Li = (int)L;
   for (int m = threadIdx.x; m <= (int)mmax; m += blockDim.x) {
     const int k = (int)((unsigned)m % (unsigned)Li), k2 = k == 0 ? 0 : Li - k;
-    const double zr = Z[2 * k], zi = Z[2 * k + 1], yr = Z[2 * k2], yi = Z[2 * k2 + 1];
+    cplx zk, zk2;
+    if constexpr (kQuad) {
+      const int ii = (int)i, sk = k / ii, sk2 = k2 / ii;
+      zk = fft_get<false>(zl, sk * P + k - sk * ii);
+      zk2 = fft_get<false>(zl, sk2 * P + k2 - sk2 * ii);
+    } else {
+      zk = {Z[2 * k], Z[2 * k + 1]};
+      zk2 = {Z[2 * k2], Z[2 * k2 + 1]};
+    }
+    const double zr = zk.r, zi = zk.i, yr = zk2.r, yi = zk2.i;
     const double nr = 0.5 * (zr + yr), ni = 0.5 * (zi - yi);    // (Z_k + conj Z_{L-k}) / 2
     const double sr = 0.5 * (zi + yi), si = -0.5 * (zr - yr);   // (Z_k - conj Z_{L-k}) / (2i)
     double sp = 0.0, cp = 1.0;
@@ -638,6 +674,21 @@ k_ring_chirp(int64_t nside, int64_t mmax, const double* map, const double* ftab,
     ring_chirp<kThreads / 4, true>(sm, nside, mmax, map, ftab, zslot, F, rn);
   else if constexpr (!kQuadOnly)
     ring_chirp<kThreads, false>(sm, nside, mmax, map, ftab, zslot, F, rn);
+}
+
+// Step 1 of a small map whose Nside is a power of two (2 .. 256): the cap ring
+// pairs and the belt rings in one launch, 256 threads each.  Neither fills the
+// chip, so the belt's transforms run beside the caps' (Nside 128: 17 + 6 us in
+// two launches, 19 in one; a call also enqueues one launch less).
+constexpr int64_t kRingsSmall = 256;
+template <int kPer>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_rings_small(int64_t nside, int64_t mmax, const double* map, const double* tab,
+              const double* ftab, double* zslot, double* F) {
+  extern __shared__ double sm[];
+  const int64_t b = blockIdx.x;
+  if (b < nside - 1) ring_chirp<64, true, kPer>(sm, nside, mmax, map, ftab, zslot, F, nside - 1 - b);
+  else ring_fft<256>(sm, nside, mmax, map, tab, ftab, F, b + 1);
 }
 
 // Step 2a: the pieces of lambda_mm(z) = g[m] sin^m(theta) for the north
@@ -869,22 +920,23 @@ __device__ __forceinline__ double wave_sum16(const double v[16]) {
   return r;
 }
 
-// Step 2b: partial a_lm of one block of 64 * kRingsPerLane ring pairs, for
+// Step 2b: partial a_lm of one block of 64 * R ring pairs, for
 // one m: part[blk * S + idx(l, m)] = sum over the block's pairs of
 // lambda_lm(z) (F_north +- F_south), the sign (-1)^(l+m).  Degrees are taken
-// eight at a time: each lane keeps the eight partial sums (real and
-// imaginary) and the wavefront sums all sixteen at once.  The 2^(600 e)
+// eight (or twice eight) at a time: each lane keeps the eight partial sums
+// (real and imaginary) and the wavefront sums all sixteen at once.  The 2^(600 e)
 // scale of a ring's lambda is carried by its two Fourier factors instead
 // (exact while they stay normal; a ring whose lambda is below 2^-177 gives
 // products far below any a_lm and may lose them), so that a step is the
 // recursion and two multiply-adds.
+template <int R, bool kDirect>
 __global__ void __launch_bounds__(256) k_legendre(int64_t nside, int64_t lmax, int64_t mmax,
                                                  const double* __restrict__ F,
                                                  const double* __restrict__ gain,
                                                  const double* __restrict__ ring_z,
                                                  const double* __restrict__ ring_s,
                                                  const double* __restrict__ coef, int64_t nblk,
-                                                 double* __restrict__ part) {
+                                                 double* __restrict__ part, double scale) {
   const int lane = threadIdx.x & 63;
   const int64_t wave = (int64_t)blockIdx.x * (blockDim.x >> 6) +
                        __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -912,8 +964,9 @@ __global__ void __launch_bounds__(256) k_legendre(int64_t nside, int64_t lmax, i
   // (the m-th derivative of P_l is a Gegenbauer polynomial of positive
   // index, largest at 1).  The bound grows with l and with sin(theta), so
   // its value at lmax on the block's most equatorial ring bounds the block.
-  {
-    const int64_t qe = min((blk + 1) * 64 * kRingsPerLane, npair) - 1;
+  // (Below lmax 1024 the bound costs more than the few blocks it would skip.)
+  if (lmax >= 1024) {
+    const int64_t qe = min((blk + 1) * 64 * R, npair) - 1;
     const double md = (double)m, Ld = (double)lmax;
     const double lg = 0.5 * log2((2.0 * Ld + 1.0) / (4.0 * 3.14159265358979323846)) +
                       md * log2(ring_s[qe]) +
@@ -925,18 +978,18 @@ __global__ void __launch_bounds__(256) k_legendre(int64_t nside, int64_t lmax, i
       return;
     }
   }
-  double z[kRingsPerLane], cur[kRingsPerLane], prev[kRingsPerLane];
-  double er[kRingsPerLane], ei[kRingsPerLane], orr[kRingsPerLane], oi[kRingsPerLane];
-  int32_t sc[kRingsPerLane];
+  double z[R], cur[R], prev[R];
+  double er[R], ei[R], orr[R], oi[R];
+  int32_t sc[R];
   // Fourier factors of pair k scaled by 2^(600 sc[k]).  The lane index is
   // re-read here through an opaque instruction so that the compiler cannot
   // hoist the reload's addresses out of the degree loop, where they would
-  // hold 2 * kRingsPerLane 64-bit registers for a path taken a few times per
+  // hold 2 * R 64-bit registers for a path taken a few times per
   // wavefront.
   auto factors = [&](int k) {
     int ln;
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
-    const int64_t q = (blk * kRingsPerLane + k) * 64 + ln;
+    const int64_t q = (blk * R + k) * 64 + ln;
     er[k] = ei[k] = orr[k] = oi[k] = 0.0;
     if (q < npair) {
       const int64_t north = q + 1;
@@ -960,8 +1013,8 @@ __global__ void __launch_bounds__(256) k_legendre(int64_t nside, int64_t lmax, i
   // rest.  The step at l = m moves it from prev to cur.
   const double gm = gain[m];
 #pragma unroll
-  for (int k = 0; k < kRingsPerLane; ++k) {
-    const int64_t q = (blk * kRingsPerLane + k) * 64 + lane;   // pair index, 0-based
+  for (int k = 0; k < R; ++k) {
+    const int64_t q = (blk * R + k) * 64 + lane;   // pair index, 0-based
     z[k] = 0.0;
     cur[k] = 0.0;
     prev[k] = 0.0;
@@ -978,12 +1031,15 @@ __global__ void __launch_bounds__(256) k_legendre(int64_t nside, int64_t lmax, i
   }
   const double big = ldexp(1.0, kLegScale);
   cdp cf = (cdp)coef;
-  // Recursion coefficients a_l of degrees l0 .. l0 + 7, the next group's
+  // Recursion coefficients a_l of degrees l0 .. l0 + G - 1, the next group's
   // requested one group ahead.  Degrees past lmax take lmax's: their steps
-  // run (every group is eight steps) but their sums are not written.
-  double cA[8];
+  // run (every group is G steps) but their sums are not written.  With one or
+  // two ring pairs per lane a wavefront has its SIMD nearly to itself and
+  // waits on the reduction's chain, so that two reductions run together.
+  constexpr int G = R <= 2 ? 16 : 8;
+  double cA[G];
 #pragma unroll
-  for (int g = 0; g < 8; ++g) cA[g] = cf[2 * (row + min((int)m + g, L))];
+  for (int g = 0; g < G; ++g) cA[g] = cf[2 * (row + min((int)m + g, L))];
   // The ring data loaded above has arrived: without this wait the loop's
   // first use of it waits on every vector memory operation in flight, the
   // previous group's store included, in every iteration.
@@ -995,16 +1051,16 @@ __global__ void __launch_bounds__(256) k_legendre(int64_t nside, int64_t lmax, i
   // the double range.  One wavefront-wide test skips the whole block when
   // no lane needs it.
   auto rescale = [&]() {
-    bool need[kRingsPerLane];
+    bool need[R];
     bool any = false;
 #pragma unroll
-    for (int k = 0; k < kRingsPerLane; ++k) {
+    for (int k = 0; k < R; ++k) {
       need[k] = sc[k] < 0 && fmax(fabs(cur[k]), fabs(prev[k])) > big;
       any |= need[k];
     }
     if (__builtin_amdgcn_ballot_w64(any)) {
 #pragma unroll
-      for (int k = 0; k < kRingsPerLane; ++k) {
+      for (int k = 0; k < R; ++k) {
         if (need[k]) {
           cur[k] = ldexp(cur[k], -kLegScale);
           prev[k] = ldexp(prev[k], -kLegScale);
@@ -1014,42 +1070,52 @@ __global__ void __launch_bounds__(256) k_legendre(int64_t nside, int64_t lmax, i
       }
     }
   };
-  for (int l0 = (int)m; l0 <= L; l0 += 8) {
-    double nA[8];
+  for (int l0 = (int)m; l0 <= L; l0 += G) {
+    double nA[G];
 #pragma unroll
-    for (int g = 0; g < 8; ++g) nA[g] = cf[2 * (row + min(l0 + 8 + g, L))];
+    for (int g = 0; g < G; ++g) nA[g] = cf[2 * (row + min(l0 + G + g, L))];
     __builtin_amdgcn_sched_barrier(0);    // issue the requests before the arithmetic
     if (((l0 - (int)m) & 31) == 0) rescale();
-    double acc[16];
+    double acc[2 * G];
 #pragma unroll
-    for (int g = 0; g < 16; ++g) acc[g] = 0.0;
+    for (int g = 0; g < 2 * G; ++g) acc[g] = 0.0;
     // Degree l0 + g: l + m has the parity of g, so even g takes
     // F_north + F_south and odd g F_north - F_south.
 #pragma unroll
-    for (int g = 0; g < 8; ++g) {
+    for (int g = 0; g < G; ++g) {
       // mu_l = (a_l z) mu_{l-1} + mu_{l-2}: the product a_l z does not wait
       // on the recursion, so the dependent chain is one FMA per degree; the
       // operations run over the lane's ring pairs one after the other.
-      double t[kRingsPerLane];
+      double t[R];
 #pragma unroll
-      for (int k = 0; k < kRingsPerLane; ++k) t[k] = cA[g] * z[k];
+      for (int k = 0; k < R; ++k) t[k] = cA[g] * z[k];
 #pragma unroll
-      for (int k = 0; k < kRingsPerLane; ++k) {
+      for (int k = 0; k < R; ++k) {
         const double nu = fma(t[k], cur[k], prev[k]);
         prev[k] = cur[k];
         cur[k] = nu;
       }
 #pragma unroll
-      for (int k = 0; k < kRingsPerLane; ++k) {
+      for (int k = 0; k < R; ++k) {
         acc[2 * g] = fma(cur[k], (g & 1) ? orr[k] : er[k], acc[2 * g]);
         acc[2 * g + 1] = fma(cur[k], (g & 1) ? oi[k] : ei[k], acc[2 * g + 1]);
       }
     }
-    const double tot = wave_sum16(acc);
-    // v: the real (even) or imaginary (odd) part of degree l0 + v/2
-    if ((lane & 3) == 0 && l0 + (v >> 1) <= L) out[2 * (row + l0) + v] = tot;
+    double tot[G / 8];
 #pragma unroll
-    for (int g = 0; g < 8; ++g) cA[g] = nA[g];
+    for (int h = 0; h < G / 8; ++h) tot[h] = wave_sum16(acc + 16 * h);
+    // v: the real (even) or imaginary (odd) part of degree l0 + 8 h + v/2
+#pragma unroll
+    for (int h = 0; h < G / 8; ++h) {
+      const int l = l0 + 8 * h + (v >> 1);
+      if ((lane & 3) == 0 && l <= L) {
+        // One block: its sums are a_lm but for the rescaling.
+        const int at = 2 * (row + l0 + 8 * h) + v;
+        out[at] = kDirect ? scale * coef[2 * (row + l) + 1] * tot[h] : tot[h];
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) cA[g] = nA[g];
   }
 }
 
@@ -1088,27 +1154,47 @@ __global__ void __launch_bounds__(256) k_alm2cl(int64_t lmax, const double* alm,
 
 }  // namespace
 
-// Doubles of the region that holds the Legendre partial sums; the cap
-// rings' Z slots (2 N (N - 1) complex values) use it first.
-static int64_t part_doubles(int64_t nside, int64_t lmax) {
-  const int64_t npair = 2 * nside;
-  const int64_t nblk = (npair + 64 * kRingsPerLane - 1) / (64 * kRingsPerLane);
+constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;
+
+static int64_t leg_blocks(int64_t nside, int rings) {
+  return (2 * nside + 64 * rings - 1) / (64 * rings);
+}
+
+// Doubles of the region that holds the Legendre partial sums; the chirp
+// transforms' Z slots (2 N (N - 1) complex values) use it first.
+static int64_t part_doubles(int64_t nside, int64_t lmax, int rings) {
   const int64_t size = (lmax + 1) * (lmax + 2) / 2;
   const int64_t zs = 4 * nside * (nside - 1);
-  return 2 * nblk * size > zs ? 2 * nblk * size : zs;
+  return std::max(2 * leg_blocks(nside, rings) * size, zs);
+}
+
+static size_t scratch_bytes(int64_t nside, int64_t lmax, int rings);
+
+// Ring pairs per lane: the most that make kLegWaves wavefronts, else one; but
+// eight wherever the blocks' sums would not fit the fixed scratch of the
+// allocation-free call, which makes the same choice and so the same results.
+static int leg_rings(int64_t nside, int64_t lmax) {
+  int r = kLegMaxRings;
+  while (r > 1 && (lmax + 1) * leg_blocks(nside, r) < kLegWaves) r /= 2;
+  while (r < kLegMaxRings && scratch_bytes(nside, lmax, r) > kNoAllocScratchBytes) r *= 2;
+  return r;
 }
 
 // Scratch needs of map2alm at (nside, lmax): bytes of the Fourier table,
 // the ring geometry, the recursion coefficients, the block partials and the
 // small tables.
-size_t map2alm_scratch_bytes(int64_t nside, int64_t lmax) {
+static size_t scratch_bytes(int64_t nside, int64_t lmax, int rings) {
   const int64_t M = lmax + 1;
   const int64_t nring = 4 * nside - 1, npair = 2 * nside;
   const int64_t size = (lmax + 1) * (lmax + 2) / 2;
   return sizeof(double) * (size_t)(2 * nring * M) + sizeof(double) * (size_t)(2 * npair) +
-         sizeof(double) * (size_t)(2 * size) + sizeof(double) * (size_t)part_doubles(nside, lmax) +
+         sizeof(double) * (size_t)(2 * size) + sizeof(double) * (size_t)part_doubles(nside, lmax, rings) +
          sizeof(double) * (size_t)(2 * (4 * nside + 1)) + sizeof(double) * (size_t)(2 * kTwP) +
          sizeof(double) * (size_t)M + 8 * 256;
+}
+
+size_t map2alm_scratch_bytes(int64_t nside, int64_t lmax) {
+  return scratch_bytes(nside, lmax, leg_rings(nside, lmax));
 }
 
 // All of map2alm on `st`; `scratch` holds map2alm_scratch_bytes(nside, lmax).
@@ -1116,7 +1202,8 @@ hipError_t launch_map2alm(int64_t nside, int64_t lmax, const double* map, double
                           void* scratch, hipStream_t st) {
   const int64_t M = lmax + 1;
   const int64_t nring = 4 * nside - 1, npair = 2 * nside;
-  const int64_t nblk = (npair + 64 * kRingsPerLane - 1) / (64 * kRingsPerLane);
+  const int rings = leg_rings(nside, lmax);
+  const int64_t nblk = leg_blocks(nside, rings);
   const int64_t size = (lmax + 1) * (lmax + 2) / 2;
   auto align = [](size_t b) { return (b + 255) & ~(size_t)255; };
   char* p = (char*)scratch;
@@ -1128,7 +1215,7 @@ hipError_t launch_map2alm(int64_t nside, int64_t lmax, const double* map, double
   double* coef = (double*)p;
   p += align(sizeof(double) * (size_t)(2 * size));
   double* part = (double*)p;
-  p += align(sizeof(double) * (size_t)part_doubles(nside, lmax));
+  p += align(sizeof(double) * (size_t)part_doubles(nside, lmax, rings));
   double* tab = (double*)p;
   p += align(sizeof(double) * (size_t)(2 * (4 * nside + 1)));
   double* ftab = (double*)p;
@@ -1166,7 +1253,17 @@ hipError_t launch_map2alm(int64_t nside, int64_t lmax, const double* map, double
     const int64_t nb = a.n_scan + 1 + a.n_zs + a.n_tab + a.n_tw;
     k_setup<<<dim3((unsigned)nb), dim3(256), 0, st>>>(a);
   }
-  if (fft) {
+  const bool small = fft && nside >= 2 && nside <= kRingsSmall;
+  if (small) {
+    const size_t lds = fft_lds_bytes(std::max(4 * pow2_at_least(2 * (nside - 1) - 1), 2 * nside));
+    auto rings = [&](auto kernel) {
+      kernel<<<dim3((unsigned)(3 * nside)), 256, lds, st>>>(nside, lmax, map, tab, ftab, part, F);
+    };
+    if (nside <= 32) rings(k_rings_small<1>);         // transforms of 64 kPer points
+    else if (nside <= 64) rings(k_rings_small<2>);
+    else if (nside <= 128) rings(k_rings_small<4>);
+    else rings(k_rings_small<8>);
+  } else if (fft) {
     const dim3 grid((unsigned)(2 * nside + 1));
     const size_t lds = fft_lds_bytes(2 * nside);
     if (2 * nside <= 8 * 512) k_ring_fft<512><<<grid, 512, lds, st>>>(nside, lmax, map, tab, ftab, F);
@@ -1182,7 +1279,7 @@ hipError_t launch_map2alm(int64_t nside, int64_t lmax, const double* map, double
       return fft_lds_bytes(i <= threads ? quad : std::max(P, quad));
     };
     auto grid = [&](int64_t to) { return dim3((unsigned)(to - lo + 1)); };
-    if (nside <= 256) {
+    if (nside <= kRingsSmall) {
       k_ring_chirp<256, true><<<grid(hi), 256, lds(256, hi), st>>>(nside, lmax, map, ftab, part, F,
                                                                   lo);
       return;
@@ -1197,10 +1294,10 @@ hipError_t launch_map2alm(int64_t nside, int64_t lmax, const double* map, double
       k_ring_chirp<1024, false><<<grid(hi), 1024, lds(1024, hi), st>>>(nside, lmax, map, ftab,
                                                                       part, F, lo);
   };
-  if (caps) chirp(1, nside - 1);
+  if (caps && !small) chirp(1, nside - 1);
   if (chirp_belt) {
     // As many belt pairs at a time as the region holds Z slots for.
-    const int64_t most = std::max<int64_t>(1, part_doubles(nside, lmax) / (8 * nside));
+    const int64_t most = std::max<int64_t>(1, part_doubles(nside, lmax, rings) / (8 * nside));
     for (int64_t r = nside; r <= 2 * nside; r += most)
       chirp(r, std::min(r + most - 1, 2 * nside));
   }
@@ -1213,10 +1310,23 @@ hipError_t launch_map2alm(int64_t nside, int64_t lmax, const double* map, double
     k_ring_dft<<<dim3((unsigned)((dft_waves + 3) / 4)), dim3(256), 0, st>>>(nside, lmax, map, F,
                                                                            lo, hi);
   }
-  const int64_t leg_waves = M * nblk;
-  k_legendre<<<dim3((unsigned)((leg_waves + 3) / 4)), dim3(256), 0, st>>>(
-      nside, lmax, lmax, F, gain, ring_z, ring_s, coef, nblk, part);
+  const dim3 leg_grid((unsigned)((M * nblk + 3) / 4));
   const double w = 4.0 * 3.14159265358979323846 / (double)(12 * nside * nside);
+  // With one block of ring pairs (Nside <= 32, where a lane always holds one)
+  // its sums go to alm at once.
+  auto legendre = [&](auto kernel, double* out) {
+    kernel<<<leg_grid, 256, 0, st>>>(nside, lmax, lmax, F, gain, ring_z, ring_s, coef, nblk, out, w);
+  };
+  if (rings == 1 && nblk == 1) {
+    legendre(k_legendre<1, true>, alm);
+    return hipGetLastError();
+  }
+  switch (rings) {
+    case 1: legendre(k_legendre<1, false>, part); break;
+    case 2: legendre(k_legendre<2, false>, part); break;
+    case 4: legendre(k_legendre<4, false>, part); break;
+    default: legendre(k_legendre<8, false>, part); break;
+  }
   k_alm_sum<<<dim3((unsigned)((size + 255) / 256)), dim3(256), 0, st>>>(size, nblk, w, part,
                                                                         coef, alm);
   return hipGetLastError();
@@ -1226,7 +1336,6 @@ hipError_t launch_map2alm(int64_t nside, int64_t lmax, const double* map, double
 // GPU, held until the process ends.  Host code reaches it only through the
 // address hipGetSymbolAddress returns on each device (the array's name is a
 // host-side stand-in there), looked up once per device and kept.
-constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;
 static __device__ __align__(256) char scratch[kNoAllocScratchBytes];
 
 size_t map2alm_noalloc_max_bytes() { return kNoAllocScratchBytes; }

@@ -45,3 +45,21 @@ def test_ring_sparse(nside, lmax):
     print("ring-sparse map", nside, lmax, flush=True)
     got = B.map2alm(torch.from_numpy(hmap).cuda(), lmax).cpu().numpy()
     assert np.max(np.abs(got - ref)) <= 1e-11 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("nside,lmax", [(2, 3), (16, 40), (32, 64), (33, 70), (64, 100), (128, 300),
+                                        (200, 30), (256, 512), (512, 600)])
+def test_ring_pairs_per_lane(nside, lmax):
+    """Every number of ring pairs per lane and degrees per group that the
+    Legendre kernel takes, with one and several blocks of ring pairs, against
+    the oracle's lambda_lm on a few rings (the same bar)."""
+    from paper_1204_5041_amd import binding as B
+    N = nside
+    rings = sorted({1, N // 2 + 1, N, 2 * N - 1, 2 * N, 3 * N, 4 * N - 1})
+    rng = np.random.Generator(np.random.PCG64(7 * nside))
+    hmap = np.zeros(12 * N * N)
+    for r in rings:
+        hmap[_first(N, r):_first(N, r) + _length(N, r)] = rng.standard_normal(_length(N, r))
+    ref = ring_sparse_alm(N, lmax, hmap, rings)
+    got = B.map2alm(torch.from_numpy(hmap).cuda(), lmax).cpu().numpy()
+    assert np.max(np.abs(got - ref)) <= 1e-11 * np.max(np.abs(ref))
