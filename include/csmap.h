@@ -335,8 +335,9 @@ typedef struct {
  * u = Xdot - (c.X')/(1 + c.Xdot) X' and u_perp = (e1.u, e2.u); a pixel at
  * t = s receives 0.  Writes map (device, ny x nx doubles, index j nx + i).
  * Segment geometry (slab, cone boxes, snapshot crossings) is that of render,
- * in FP64; the pair sum is FP32 with compensated accumulation, whatever the
- * sky's form.  stats report the light-cone stage and the record pass as
+ * in FP64; the terms of segments near a pixel (within about 70 pixels) are
+ * FP32 with compensated accumulation, those of the others FP64 power series
+ * that leave out less than 5e-10 of a term, whatever the sky's form.  stats report the light-cone stage and the record pass as
  * ms_precompute and the pair kernel as ms_forward.  Enqueued on the sky's
  * stream.  CSMAP_E_INVALID for accept_cos outside (0, 1] or an acceptance
  * cone so wide that tan(acos(accept_cos))/pix + max(nx, ny) > 2^30 (the

@@ -35,8 +35,9 @@ hipError_t launch_ang2pix(int64_t nside, int64_t n, const double* xyz, int64_t* 
 hipError_t launch_flat(const FlatArgs& A, hipStream_t st);
 hipError_t launch_dirs_soa(int64_t n, const double* xyz, double* x, double* y, double* z,
                            hipStream_t st);
-hipError_t launch_flat_pairs(const FlatArgs& A, int64_t nsplit, double* part, hipStream_t st);
-int64_t flat_splits(int64_t nx, int64_t ny);
+FlatPlan flat_plan(int64_t nx, int64_t ny, int64_t nseg, double reach);
+hipError_t launch_flat_pairs(const FlatArgs& A, const FlatPlan& plan, double* scratch,
+                             hipStream_t st);
 hipError_t launch_dir_table(int64_t nside, int64_t npix, double* x, double* y, double* z,
                             hipStream_t st);
 hipError_t launch_cone_events(int64_t n, int dtype, const void* x_rel, const void* xdot,
@@ -169,7 +170,7 @@ struct csmap_sky {
   int32_t *p_blk_box = nullptr, *p_tile_ptr = nullptr, *p_tile_boxes = nullptr;
   int32_t* p_box_items = nullptr;
   WorkItem* p_work = nullptr;
-  DevBuf d_flat_off, d_flat_rec, d_flat_part;
+  DevBuf d_flat_off, d_flat_rec, d_flat_pos, d_flat_part;
   DevBuf d_udir;      // caller directions of csmap_render_dirs, x | y | z
   DevBuf d_part;      // partial tiles of record slices (render; held by a captured graph)
   DevBuf d_udir_part; // csmap_render_dirs: the same
@@ -812,8 +813,8 @@ csmap_status csmap_destroy_sky(csmap_sky* s) {
   if (s->up_ev) (void)hipEventDestroy(s->up_ev);
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
   DevBuf* bufs[] = {&s->raw, &s->d_blk_count, &s->d_blk_prefix, &s->d_box_count, &s->d_blk_mask,
-                    &s->d_plan, &s->d_flat_off, &s->d_flat_rec, &s->d_flat_part, &s->d_udir,
-                    &s->d_part, &s->d_udir_part, &s->d_rows, &s->d_frames, &s->d_rec32,
+                    &s->d_plan, &s->d_flat_off, &s->d_flat_rec, &s->d_flat_pos, &s->d_flat_part,
+                    &s->d_udir, &s->d_part, &s->d_udir_part, &s->d_rows, &s->d_frames, &s->d_rec32,
                     &s->d_recm, &s->d_phat64, &s->d_rec64, &s->d_orig, &s->d_counters,
                     &s->d_pixtab32, &s->d_pix64, &s->d_partial, &s->d_adj_items, &s->d_adjc,
                     &s->d_dir};
@@ -1325,22 +1326,23 @@ csmap_status csmap_render_flat(csmap_sky* s, const csmap_patch* patch, double* m
   // tan(rho)/pix + n, and with that bound at 2^30 the pair kernel's product
   // of two squared distances stays below 4 (2^30)^4 = 2^122, inside the range
   // of its reciprocal ([2^-125, 2^125]).
-  {
-    const double c = P.accept_cos;
-    const double tan_rho = sqrt((1.0 - c) * (1.0 + c)) / c;
-    const double nmax = (double)std::max(P.nx, P.ny);
-    if (!(tan_rho / P.pix + nmax <= 1073741824.0))
-      return fail(CSMAP_E_INVALID,
-                  "acceptance cone too wide for the pixel size: need "
-                  "tan(acos(accept_cos))/pix + max(nx, ny) <= 2^30");
-  }
+  const double tan_rho = sqrt((1.0 - P.accept_cos) * (1.0 + P.accept_cos)) / P.accept_cos;
+  if (!(tan_rho / P.pix + (double)std::max(P.nx, P.ny) <= 1073741824.0))
+    return fail(CSMAP_E_INVALID,
+                "acceptance cone too wide for the pixel size: need "
+                "tan(acos(accept_cos))/pix + max(nx, ny) <= 2^30");
   cs = prepare(s);
   if (cs != CSMAP_OK) return cs;
   const int64_t nbox = (int64_t)s->boxes.size();
   hipStream_t st = s->stream;
   HIPCHK(s, s->d_flat_off.ensure(sizeof(int64_t) * (nbox + 1)), "alloc flat offsets");
-  HIPCHK(s, s->d_flat_rec.ensure(sizeof(float) * kFlatRec * (size_t)(s->total_seg + 2)),
+  HIPCHK(s, s->d_flat_rec.ensure(sizeof(float) * kFlatRec * (size_t)s->total_seg),
          "alloc flat records");
+  HIPCHK(s, s->d_flat_pos.ensure(sizeof(float2) * (size_t)s->total_seg), "alloc flat positions");
+  const FlatPlan plan = flat_plan(P.nx, P.ny, s->total_seg, tan_rho / P.pix);
+  HIPCHK(s, s->d_flat_part.ensure(sizeof(double) * (size_t)(plan.part_doubles + plan.lv_doubles +
+                                                            plan.up_doubles)),
+         "alloc flat sums");
   PreArgs pa = pre_args(s);
   pa.flat_on = 1;
   for (int k = 0; k < 3; ++k) pa.flat_dir[k] = P.center[k];
@@ -1368,16 +1370,13 @@ csmap_status csmap_render_flat(csmap_sky* s, const csmap_patch* patch, double* m
   A.ny = P.ny;
   A.flat_off = s->d_flat_off.as<int64_t>();
   A.rec = s->d_flat_rec.as<float>();
+  A.pos = s->d_flat_pos.as<float2>();
   A.map = map;
   HIPCHK(s, hipEventRecord(s->ev[0], st), "event");
   HIPCHK(s, launch_precompute(pa, nbox, st), "precompute launch");
   HIPCHK(s, launch_flat(A, st), "flat record launch");
   HIPCHK(s, hipEventRecord(s->ev[1], st), "event");
-  const int64_t nsplit = flat_splits(P.nx, P.ny);
-  if (nsplit > 1)
-    HIPCHK(s, s->d_flat_part.ensure(sizeof(double) * (size_t)nsplit * (size_t)(P.nx * P.ny)),
-           "alloc flat partial maps");
-  HIPCHK(s, launch_flat_pairs(A, nsplit, s->d_flat_part.as<double>(), st), "flat pair launch");
+  HIPCHK(s, launch_flat_pairs(A, plan, s->d_flat_part.as<double>(), st), "flat pair launch");
   HIPCHK(s, hipEventRecord(s->ev[2], st), "event");
   s->timed_graph = false;
   s->have_fwd_time = true;

@@ -117,11 +117,30 @@ struct FlatArgs {
   double inv_h;                // 1 / pixel size (radians)
   double off_x, off_y;         // pixel coordinate of the axis: n/2 - 1/2
   int64_t nx, ny;
-  int64_t* flat_off;           // [nbox + 1]: first flat record of each box; [nbox]: total (even)
+  int64_t* flat_off;           // [nbox + 1]: first flat record of each box; [nbox]: total
   float* rec;                  // kFlatRec floats per flat record
+  float2* pos;                 // plane position of each flat record, in pixels
   double* map;                 // ny x nx, row-major
 };
 constexpr int kFlatRec = 8;
+
+// Square tiles of a patch, with one power series each (if `series` is 1) over segments farther
+// than sqrt(near2) pixels from the tile's centre, in nsplit record ranges:
+// coef[(range ntiles + tile) 2 terms + 2 k], [.. + 1] = Re, Im L_k.
+struct FlatLevel {
+  int64_t tx, ntiles;   // tiles per row of tiles, and in all
+  int64_t nsplit;
+  double rho, inv_rho;  // farthest pixel centre from the tile's centre
+  double* coef;
+  float near2;
+  int32_t side;
+  int32_t series;
+};
+
+struct FlatPlan {
+  FlatLevel lv, up;     // the finer tiles, which also own the near sums, and the coarser
+  int64_t part_doubles, lv_doubles, up_doubles;
+};
 
 // Frame of a tile of the forward launch: its centre c (the normalised mean of
 // its pixel directions), tangent axes e1 and e2, and the largest angle rho of
