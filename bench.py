@@ -115,7 +115,7 @@ def main():
                          "12 Nside_c=1 cones (light-cone stage of 3084 placed boxes); flat: "
                          "flat-sky small-angle map of a 7.2 degree 1024^2 patch from 2M "
                          "segments; counters: one launch each of a known-FMA probe (FP32, "
-                         "FP64), the bench step's k_fwd32 and k_fwd64, the config4 adjoint "
+                         "FP64), the bench step's k_fwd32m and k_fwd64, the config4 adjoint "
                          "and map2alm, for hardware counter runs; hbm: the streaming rate of "
                          "a plain device copy, the yardstick for the HBM-bound kernels")
     ap.add_argument("--stack-seg", type=int, default=200_000,
@@ -228,15 +228,17 @@ def main():
                    "pairs_per_step": pairs_per_step, "tile": cfg},
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP32_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / FP32_PEAK_TFLOPS,
-                     "traffic": measured_traffic("k_fwd32") if args.nseg == NSEG and args.nside == NSIDE
+                     "traffic": measured_traffic("k_fwd32m") if args.nseg == NSEG and args.nside == NSIDE
                      else None,
-                     "kernel": "k_fwd32", "kernel_ms": kern_s * 1e3,
-                     "flop_per_pair": FLOP_PER_PAIR},
+                     "kernel": "k_fwd32m", "kernel_ms": kern_s * 1e3,
+                     "flop_per_pair": FLOP_PER_PAIR,
+                     "note": "peak is the FP32 vector one; the dot products of a pair run on "
+                             "the bf16 matrix cores in split precision"},
     }
     if args.nseg == NSEG and args.nside == NSIDE:
         # Hardware-counted FLOP of this launch (rocprofv3 counters of the same
         # kernel on the same box size), over the launch time measured here.
-        hw = measured_valu("k_fwd32", kern_s * 1e3)
+        hw = measured_valu("k_fwd32m", kern_s * 1e3)
         out["roofline"]["hw"] = hw
         out["roofline"]["hw_tflops"] = hw["fp32_tflops"] if hw else None
     del skies
@@ -639,8 +641,8 @@ def bench_flat(args, B, torch):
     patch at the north pole, 1024 x 1024 pixels of 0.42', and 2,000,000 FP32
     segments in the 6 degree cap behind it between 1.4 and 15.5 Gpc.  One
     step is csmap_render_flat: the light-cone stage with the patch's
-    acceptance cone, the record pass, and the FP32 pair kernel (timed with
-    HIP events on the sky's stream)."""
+    acceptance cone, the record pass, and the tiles' series and near sums (timed
+    with HIP events on the sky's stream)."""
     import oracle
     import synth
     fp = synth.flat_pencil()
@@ -677,10 +679,12 @@ def bench_flat(args, B, torch):
                       "kept": kept, "pairs_per_step": pairs,
                       "ms_light_cone_and_records": sum(pre_ms) / K,
                       "ms_pairs": sum(pair_ms) / K},
-           "roofline": {"bound": "alu", "achieved": tf, "peak": FP32_PEAK_TFLOPS,
-                        "unit": "TFLOP/s", "frac": tf / FP32_PEAK_TFLOPS, "traffic": None,
-                        "kernel": "k_flat32", "kernel_ms": k_avg * 1e3,
-                        "flop_per_pair": FLAT_FLOP_PER_PAIR}}
+           # Pairs are an effective count: most segments act on a tile's pixels
+           # through its power series, so 10 FLOP a pair are not issued.
+           "roofline": {"bound": "alu", "achieved": None, "peak": FP32_PEAK_TFLOPS,
+                        "unit": "TFLOP/s", "frac": None, "traffic": None,
+                        "kernel": "k_flat_far + k_flat_near", "kernel_ms": k_avg * 1e3,
+                        "pair_by_pair_tflops": tf, "flop_per_pair": FLAT_FLOP_PER_PAIR}}
     m = out.cpu().numpy()
     sky.close()
     res["fig3_style"] = flat_vs_full(B, torch, fp)
@@ -886,13 +890,13 @@ def measured_valu(kernel, kernel_ms):
 VALU_SOURCES = {
     # The kernel sources, and the host code that chooses its launch (tiling,
     # tile plan), which changes what the counters see.
-    "k_fwd32": ["paper_1204_5041_amd/csrc/kernels.hip", "paper_1204_5041_amd/csrc/segment_dev.h",
-                "paper_1204_5041_amd/csrc/internal.h", "paper_1204_5041_amd/csrc/healpix_dev.h",
-                "paper_1204_5041_amd/csrc/api.cpp", "paper_1204_5041_amd/csrc/sched.cpp"],
+    "k_fwd32m": ["paper_1204_5041_amd/csrc/kernels.hip", "paper_1204_5041_amd/csrc/segment_dev.h",
+                 "paper_1204_5041_amd/csrc/internal.h", "paper_1204_5041_amd/csrc/healpix_dev.h",
+                 "paper_1204_5041_amd/csrc/api.cpp", "paper_1204_5041_amd/csrc/sched.cpp"],
     "k_legendre": ["paper_1204_5041_amd/csrc/alm.hip", "paper_1204_5041_amd/csrc/healpix_dev.h"],
     "k_valu_probe": ["paper_1204_5041_amd/csrc/probe.hip"],
 }
-VALU_SOURCES["k_fwd64"] = VALU_SOURCES["k_adj32"] = VALU_SOURCES["k_fwd32"]
+VALU_SOURCES["k_fwd64"] = VALU_SOURCES["k_adj32"] = VALU_SOURCES["k_fwd32m"]
 
 
 def _sources_sha(files):
@@ -947,7 +951,7 @@ def summarize_counters(trace_dir, pmc_a, pmc_b, launches_json):
     plan = [("k_valu_probe<float, false>", "probe_fp32", None),
             ("k_valu_probe<double, false>", "probe_fp64", None),
             ("k_valu_probe<float, true>", "probe_fp32_scalar_operand", None),
-            ("k_fwd32", "k_fwd32", ("k_fwd32", 0)),
+            ("k_fwd32m", "k_fwd32m", ("k_fwd32m", 0)),
             ("k_fwd64", "k_fwd64", ("k_fwd64", 0)),
             ("k_adj32", "k_adj32", ("k_adj32", 0)),
             ("k_legendre", "k_legendre", None)]
@@ -1019,7 +1023,7 @@ def bench_counters(args, B, torch):
     seeded random map six times (k_legendre; its work does not depend on the
     values; the summaries take the last call, once the clock has risen from
     its idle level), the default step's
-    k_fwd32 (config2 box 0, FP32C), k_fwd64 (same box, FP64 form) and the
+    k_fwd32m (config2 box 0, FP32C), k_fwd64 (same box, FP64 form) and the
     config4 adjoint (k_adj32)."""
     import synth
     res = {"metric": "counter-run launches"}
@@ -1042,11 +1046,11 @@ def bench_counters(args, B, torch):
     res["map2alm"] = {"nside": NSIDE, "lmax": 4096, "calls": 6,
                       "ms_last": (time.perf_counter() - t0) * 1e3}
     del hm
-    _log("counters: k_fwd32 (config2 box 0)")
+    _log("counters: k_fwd32m (config2 box 0)")
     sky, box = make_sky(B, torch, 0, B.CSMAP_FORM_FP32C, NSEG, NSIDE)
     sky.render()
     st = sky.stats()
-    res["k_fwd32"] = {"pairs": st["pairs"], "ms": st["ms_forward"]}
+    res["k_fwd32m"] = {"pairs": st["pairs"], "ms": st["ms_forward"]}
     sky.close()
     _log("counters: k_fwd64 (config2 box 0)")
     sky, _ = make_sky(B, torch, 0, B.CSMAP_FORM_FP64, NSEG, NSIDE)
