@@ -27,7 +27,7 @@ hipError_t launch_precompute(const PreArgs& A, int64_t nbox, hipStream_t st);
 hipError_t launch_copy_box(void* dst, const void* const src[4], int64_t n, size_t es,
                            hipStream_t st);
 hipError_t launch_fill(double* p, int64_t n, double v, hipStream_t st);
-hipError_t launch_zero_counters(unsigned long long* c, int n, uint32_t* work, hipStream_t st);
+hipError_t launch_zero_counters(unsigned long long* c, hipStream_t st);
 hipError_t launch_pix2vec(int64_t nside, int64_t first, int64_t count, double* xyz,
                           hipStream_t st);
 hipError_t launch_ang2pix(int64_t nside, int64_t n, const double* xyz, int64_t* pix,
@@ -185,8 +185,7 @@ struct csmap_sky {
   int32_t nsplit = 1;
   int32_t max_slices = 1;
   bool all_boxes = true;
-  DevBuf d_counters;  // [0] pairs, [1] FP64 steps, [2] work counter (uint32), [3] middle steps,
-                      // [4] all steps
+  DevBuf d_counters;  // kCounters of a launch
   DevBuf d_dir;       // pixel directions, x | y | z (npix doubles each)
   bool dir_ready = false;
 
@@ -411,7 +410,7 @@ csmap_status prepare(csmap_sky* s) {
     HIPCHK(s, s->d_rec64.ensure(sizeof(double) * kRec64 * nrec), "alloc records");
   }
   HIPCHK(s, s->d_phat64.ensure(sizeof(double) * 4 * nrec), "alloc records");
-  HIPCHK(s, s->d_counters.ensure(64), "alloc counters");
+  HIPCHK(s, s->d_counters.ensure(sizeof(unsigned long long) * kCounters), "alloc counters");
   if (!s->dir_ready) {
     HIPCHK(s, s->d_dir.ensure(sizeof(double) * 3 * (size_t)s->npix), "alloc direction table");
     double* d = s->d_dir.as<double>();
@@ -604,7 +603,7 @@ FwdArgs fwd_args(csmap_sky* s, double* map) {
   while ((1 << A.ring_shift) * A.ring_g < 64) ++A.ring_shift;
   A.items = nullptr;
   A.nitems = s->ntiles;
-  A.work_counter = (uint32_t*)(s->d_counters.as<unsigned long long>() + 2);
+  A.work_counter = (uint32_t*)(s->d_counters.as<unsigned long long>() + kWorkCounter);
   A.nside = s->nside;
   A.npix = s->npix;
   A.eta0 = s->eta0;
@@ -673,6 +672,17 @@ unsigned persistent_grid(const csmap_sky* s) {
   return (unsigned)std::max(1, cus * per_cu);
 }
 
+// The launch's counters, each the sum of its sets.
+hipError_t read_counters(const csmap_sky* s, unsigned long long out[5]) {
+  unsigned long long c[kCounters];
+  const hipError_t e = hipMemcpy(c, s->d_counters.p, sizeof(c), hipMemcpyDeviceToHost);
+  std::fill(out, out + 5, 0ull);
+  if (e == hipSuccess)
+    for (int i = 0; i < kWorkCounter; ++i)
+      if (i % kCounterStride < 5) out[i % kCounterStride] += c[i];
+  return e;
+}
+
 // The sky's pair sums over A's work items with its present settings.
 hipError_t sky_forward(const csmap_sky* s, bool persistent, const FwdArgs& A, hipStream_t st) {
   const unsigned waves = (unsigned)s->waves;
@@ -699,8 +709,7 @@ csmap_status enqueue_render(csmap_sky* s, double* map, hipStream_t st, bool with
   if (cs != CSMAP_OK) return cs;
   if (with_events) HIPCHK(s, hipEventRecord(s->ev[0], st), "event");
   HIPCHK(s, launch_precompute(P, (int64_t)s->boxes.size(), st), "precompute launch");
-  HIPCHK(s, launch_zero_counters(s->d_counters.as<unsigned long long>(), 5,
-                                 (uint32_t*)(s->d_counters.as<unsigned long long>() + 2), st),
+  HIPCHK(s, launch_zero_counters(s->d_counters.as<unsigned long long>(), st),
          "counter reset");
   if (with_events) HIPCHK(s, hipEventRecord(s->ev[1], st), "event");
   if (s->schedule == 2) {
@@ -987,8 +996,7 @@ csmap_status csmap_precompute(csmap_sky* s) {
   const PreArgs P = pre_args(s);
   HIPCHK(s, hipEventRecord(s->ev[0], st), "event");
   HIPCHK(s, launch_precompute(P, (int64_t)s->boxes.size(), st), "precompute launch");
-  HIPCHK(s, launch_zero_counters(s->d_counters.as<unsigned long long>(), 5,
-                                 (uint32_t*)(s->d_counters.as<unsigned long long>() + 2), st),
+  HIPCHK(s, launch_zero_counters(s->d_counters.as<unsigned long long>(), st),
          "counter reset");
   HIPCHK(s, hipEventRecord(s->ev[1], st), "event");
   HIPCHK(s, hipEventRecord(s->ev[2], st), "event");
@@ -1432,8 +1440,7 @@ csmap_status csmap_render_dirs(csmap_sky* s, int64_t n, const double* xyz, doubl
   HIPCHK(s, launch_dirs_soa(n, xyz, d, d + n, d + 2 * n, st), "direction launch");
   HIPCHK(s, hipEventRecord(s->ev[0], st), "event");
   HIPCHK(s, launch_precompute(P, (int64_t)s->boxes.size(), st), "precompute launch");
-  HIPCHK(s, launch_zero_counters(s->d_counters.as<unsigned long long>(), 5,
-                                 (uint32_t*)(s->d_counters.as<unsigned long long>() + 2), st),
+  HIPCHK(s, launch_zero_counters(s->d_counters.as<unsigned long long>(), st),
          "counter reset");
   HIPCHK(s, hipEventRecord(s->ev[1], st), "event");
   if (ntiles > 0) {
@@ -1555,8 +1562,8 @@ csmap_status csmap_get_stats(csmap_sky* s, csmap_stats* out) {
   out->nbox = (int64_t)s->boxes.size();
   out->segments = s->total_seg;
   if (!s->dirty && s->d_counters.p) {
-    unsigned long long c[5] = {0, 0, 0, 0, 0};
-    HIPCHK(s, hipMemcpy(c, s->d_counters.p, sizeof(c), hipMemcpyDeviceToHost), "read counters");
+    unsigned long long c[5];
+    HIPCHK(s, read_counters(s, c), "read counters");
     out->pairs = (int64_t)c[0];
     out->near_steps = (int64_t)c[1];
     out->mid_steps = (int64_t)c[3];
@@ -1775,9 +1782,9 @@ csmap_status csmap_autotune(csmap_sky* s, const char* cache_path) {
     }
     if (r != CSMAP_OK) return r;
     double ms_min = 1e300;
-    unsigned long long ctr[5] = {0, 0, 0, 0, 0};
+    unsigned long long ctr[5];
     for (int rep = 0; rep < 3; ++rep) {
-      HIPCHK(s, launch_zero_counters(s->d_counters.as<unsigned long long>(), 5, A.work_counter, st),
+      HIPCHK(s, launch_zero_counters(s->d_counters.as<unsigned long long>(), st),
              "counter reset");
       HIPCHK(s, hipEventRecord(s->ev[0], st), "event");
       HIPCHK(s, sky_forward(s, c.S == 1, A, st), "forward launch");
@@ -1787,8 +1794,7 @@ csmap_status csmap_autotune(csmap_sky* s, const char* cache_path) {
       HIPCHK(s, hipEventElapsedTime(&ms, s->ev[0], s->ev[1]), "elapsed");
       if (rep > 0) ms_min = std::min(ms_min, (double)ms);
     }
-    HIPCHK(s, hipMemcpy(ctr, s->d_counters.p, sizeof(ctr), hipMemcpyDeviceToHost),
-           "read counters");
+    HIPCHK(s, read_counters(s, ctr), "read counters");
     *rate = (double)ctr[0] / std::max(ms_min, 1e-6) * 1e3;
     if (log)
       fprintf(stderr,

@@ -152,6 +152,22 @@ struct TileFrame {
   float rho;
 };
 
+// Counters of a launch: kCounterSlots sets of a 128-byte line each ([0] pairs,
+// [1] FP64 steps, [3] middle steps, [4] all steps; a workgroup adds to the set
+// of its index, so that workgroups of one XCD share it, and the host adds the
+// sets), then the work counter on a line of its own.  On one line every
+// addition of every wavefront queued behind the others', some 10 ns each: with
+// a short item per wavefront that was the launch's time (a pass over 2000 FP64
+// segments at Nside 64: 246 us on one line, 144 now; 20,000 FP32 segments in
+// 30,000 directions: 932 and 442 us).
+constexpr int kCounterSlots = 64, kCounterStride = 16;
+constexpr int kWorkCounter = kCounterSlots * kCounterStride;
+constexpr int kCounters = kWorkCounter + kCounterStride;
+// Persistent launches of at most this many items per wavefront (workgroup, on
+// the matrix cores) go round in the items' order of cost instead of asking
+// the work counter for each.
+constexpr int64_t kStaticRounds = 4;
+
 // A unit of forward work: slice `slice` of the `slices` into which the records
 // seen by a tile are cut (box_records).  With one slice the tile's sums go to
 // the map; otherwise to partial tile slot + slice (64 K doubles, pixel slot j

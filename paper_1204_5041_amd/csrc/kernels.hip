@@ -534,9 +534,8 @@ __global__ void __launch_bounds__(256) k_copy_box(CopyBox c) {
     if (first + 256 * j < c.end[3]) c.dst[first + 256 * j] = v[j];
 }
 
-__global__ void k_zero_counters(unsigned long long* c, int n, uint32_t* work) {
-  if (threadIdx.x < (unsigned)n) c[threadIdx.x] = 0ull;
-  if (threadIdx.x == 0 && work) *work = 0u;
+__global__ void k_zero_counters(unsigned long long* c) {
+  for (int i = threadIdx.x; i < kCounters; i += blockDim.x) c[i] = 0ull;
 }
 
 // Direction table in structure-of-arrays form (x, y, z each npix doubles).
@@ -569,12 +568,13 @@ __global__ void k_pix2vec(int64_t nside, int64_t first, int64_t count, double* x
 // ---------------------------------------------------------------------------
 // Forward pair kernels.
 // ---------------------------------------------------------------------------
+// The wavefront's next item: each starts with the item of its own index.
 __device__ __forceinline__ int64_t next_item(const FwdArgs& A, bool persistent, int lane,
                                              int64_t cur, int64_t stride) {
-  if (!persistent) return cur + stride;
+  if (!persistent || A.nitems <= kStaticRounds * stride) return cur + stride;
   uint32_t it = 0;
   if (lane == 0) it = atomicAdd(A.work_counter, 1u);
-  return (int64_t)__builtin_amdgcn_readfirstlane(__shfl(it, 0));
+  return stride + (int64_t)__builtin_amdgcn_readfirstlane(__shfl(it, 0));
 }
 
 // The pixels of one lane in a tile: slot j is pixel first + pos0 + j step,
@@ -911,7 +911,7 @@ __global__ void __launch_bounds__(256) k_fwd32(FwdArgs A) {
   // The wavefront index is uniform; say so, so that everything derived from
   // it (tile, box, segment index) lives in scalar registers.
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int64_t item = PERSISTENT ? next_item(A, true, lane, 0, 0) : (int64_t)blockIdx.x * wpb + wave;
+  int64_t item = (int64_t)blockIdx.x * wpb + wave;
   const int64_t stride = (int64_t)gridDim.x * wpb;
   unsigned long long near_steps = 0, mid_steps = 0, all_steps = 0, pairs = 0;
   const float near_w = A.near_w, far_w = A.far_w;
@@ -1099,10 +1099,11 @@ __global__ void __launch_bounds__(256) k_fwd32(FwdArgs A) {
   }
   // One atomic per wavefront and counter: per box and tile they queued up on
   // one address.
-  if (lane == 0 && pairs) atomicAdd(A.pairs, pairs);
-  if (lane == 0 && near_steps) atomicAdd(A.near_steps, near_steps);
-  if (lane == 0 && mid_steps) atomicAdd(A.mid_steps, mid_steps);
-  if (lane == 0 && all_steps) atomicAdd(A.steps, all_steps);
+  const int slot = kCounterStride * (int)(blockIdx.x % kCounterSlots);
+  if (lane == 0 && pairs) atomicAdd(A.pairs + slot, pairs);
+  if (lane == 0 && near_steps) atomicAdd(A.near_steps + slot, near_steps);
+  if (lane == 0 && mid_steps) atomicAdd(A.mid_steps + slot, mid_steps);
+  if (lane == 0 && all_steps) atomicAdd(A.steps + slot, all_steps);
 }
 
 // ---------------------------------------------------------------------------
@@ -1312,14 +1313,7 @@ k_fwd32m(FwdArgs A) {
   const cf4p recs = (cf4p)A.rec32;
   const cd2p ph64 = (cd2p)A.phat64;
   int64_t item = blockIdx.x;
-  while (true) {
-    if constexpr (PERSISTENT) {
-      if (threadIdx.x == 0) next = atomicAdd(A.work_counter, 1u);
-      __syncthreads();
-      item = __builtin_amdgcn_readfirstlane(next);
-      __syncthreads();
-    }
-    if (item >= A.nitems) break;
+  while (item < A.nitems) {
     const WorkItem wi = work_item(A, item);
     const int64_t tile = wi.tile;
     const cframe_p fr = (cframe_p)A.frames + tile;   // scalar loads
@@ -1530,14 +1524,21 @@ k_fwd32m(FwdArgs A) {
         A.map[p2[h]] = A.accumulate ? A.map[p2[h]] + out[h] : out[h];
       }
     }
-    if constexpr (!PERSISTENT) {
+    if (PERSISTENT && A.nitems > kStaticRounds * gridDim.x) {
+      if (threadIdx.x == 0) next = atomicAdd(A.work_counter, 1u);
+      __syncthreads();
+      item = (int64_t)gridDim.x + __builtin_amdgcn_readfirstlane(next);
+      __syncthreads();
+    } else {
+      __syncthreads();   // every wavefront is done with the staged rows
       item += gridDim.x;
     }
   }
-  if (lane == 0 && pairs) atomicAdd(A.pairs, pairs);
-  if (lane == 0 && near_steps) atomicAdd(A.near_steps, near_steps);
-  if (lane == 0 && mid_steps) atomicAdd(A.mid_steps, mid_steps);
-  if (lane == 0 && all_steps) atomicAdd(A.steps, all_steps);
+  const int slot = kCounterStride * (int)(blockIdx.x % kCounterSlots);
+  if (lane == 0 && pairs) atomicAdd(A.pairs + slot, pairs);
+  if (lane == 0 && near_steps) atomicAdd(A.near_steps + slot, near_steps);
+  if (lane == 0 && mid_steps) atomicAdd(A.mid_steps + slot, mid_steps);
+  if (lane == 0 && all_steps) atomicAdd(A.steps + slot, all_steps);
 }
 
 __device__ __forceinline__ double rcp_f64(double x) {
@@ -1652,7 +1653,7 @@ __global__ void __launch_bounds__(256) k_fwd64(FwdArgs A) {
   // The wavefront index is uniform; say so, so that everything derived from
   // it (tile, box, segment index) lives in scalar registers.
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int64_t item = PERSISTENT ? next_item(A, true, lane, 0, 0) : (int64_t)blockIdx.x * wpb + wave;
+  int64_t item = (int64_t)blockIdx.x * wpb + wave;
   const int64_t stride = (int64_t)gridDim.x * wpb;
   cd2p recs = (cd2p)A.rec64;
   unsigned long long pairs = 0;
@@ -1728,7 +1729,8 @@ __global__ void __launch_bounds__(256) k_fwd64(FwdArgs A) {
     }
     item = PERSISTENT ? next_item(A, true, lane, item, stride) : item + stride;
   }
-  if (lane == 0 && pairs) atomicAdd(A.pairs, pairs);
+  const int slot = kCounterStride * (int)(blockIdx.x % kCounterSlots);
+  if (lane == 0 && pairs) atomicAdd(A.pairs + slot, pairs);
 }
 
 // The map's pixels of the sliced tiles: each the sum of its tile's partial
@@ -2193,8 +2195,8 @@ hipError_t launch_fill(double* p, int64_t n, double v, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_zero_counters(unsigned long long* c, int n, uint32_t* work, hipStream_t st) {
-  k_zero_counters<<<1, 64, 0, st>>>(c, n, work);
+hipError_t launch_zero_counters(unsigned long long* c, hipStream_t st) {
+  k_zero_counters<<<1, 256, 0, st>>>(c);
   return hipGetLastError();
 }
 
